@@ -81,6 +81,8 @@ def attn_source_hash():
     flags)."""
     h = hashlib.sha256()
     for rel in (("paper_2604_09603_amd", "csrc", "attn.hip"),
+                ("paper_2604_09603_amd", "csrc", "attn_core.h"),
+                ("paper_2604_09603_amd", "csrc", "attn_wide.h"),
                 ("paper_2604_09603_amd", "csrc", "attn_device.h"),
                 ("paper_2604_09603_amd", "build.py")):
         with open(os.path.join(ROOT, *rel), "rb") as f:

@@ -29,11 +29,15 @@
 //                 lies inside one range is normalised and written to out/lse; a
 //                 cut unit leaves one partial (O, max, sums) per stream and
 //                 workgroup.
+//   attn_wide     instead of attn_main where many rows share a KV head (see
+//                 attn_is_wide and attn_wide.h).
 //   attn_combine  one thread per (cut unit, stream, two rows, 4 dims): merges the
 //                 partials in range order (deterministic) into out and lse.
 #include <hip/hip_ext.h>
 
+#include "attn_core.h"
 #include "attn_device.h"
+#include "attn_wide.h"
 #include "echo_device.h"
 #include "echo_internal.h"
 
@@ -58,11 +62,12 @@ __global__ __launch_bounds__(kPageChunk) void attn_pages_kernel(KvSource kv) {
   if (threadIdx.x == 0) const_cast<int32_t*>(kv.page_bad)[size_t(r) * kv.page_chunks + c] = bad;
 }
 
+template <bool kWide>
 __global__ __launch_bounds__(kThreads) void attn_plan_kernel(
     const int32_t* __restrict__ q_offsets, KvSource kv, int R, int hkv, int G, int max_rows,
     int nb, long long ucap, AttnWs ws, int32_t* status) {
   extern __shared__ int32_t plan_tables[];  // plan_table_words(min(R, kThreads))
-  plan_body<kThreads>(q_offsets, kv, R, hkv, G, max_rows, nb, ucap, ws, status, plan_tables);
+  plan_body<kThreads, kWide>(q_offsets, kv, R, hkv, G, max_rows, nb, ucap, ws, status, plan_tables);
 }
 
 // ---------------------------------------------------------------- main ----
@@ -74,42 +79,13 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(
 // the transposed V reads of two 16-lane blocks (8 rows, 4 at a time, of 2
 // consecutive chunks: the rows' low bits select the chunk's high bits and
 // the next two bits its low bits).
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef short shortx4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) shortx4 lds_shortx4_t;
-
 constexpr int kTileBytes = kTileKeys * kD * 2;  // 8 KB per tensor
 constexpr int kStageBytes = 2 * kTileBytes;     // K then V
 constexpr int kMainLds = kWaves * kWaveStages * kStageBytes;  // 128 KB
 static_assert(kMainLds <= 160 * 1024, "gfx950 LDS per workgroup");
 
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// Round two floats to bfloat16 (to nearest even) in one v_cvt_pk_bf16_f32.
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
-}
-
-// acc plus the two bfloat16 values packed in w (one v_dot2c_f32_bf16 against
-// (1, 1); the products are exact).
-__device__ __forceinline__ float add_bf16x2(uint32_t w, float acc) {
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w),
-                                         __builtin_bit_cast(bf16x2, 0x3F803F80u), acc, false);
-}
-
-__device__ __forceinline__ int swz_pattern(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-
 __device__ __forceinline__ int swz(int row, int chunk) {
   return row * 256 + ((chunk ^ swz_pattern(row)) << 4);
-}
-
-__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(x));
-  const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(x >> 32));
-  return (uint64_t(hi) << 32) | lo;
 }
 
 constexpr int kCopiesPerTile = 16;  // wave instructions of 1 KB (4 key rows) per K+V tile
@@ -246,18 +222,6 @@ __device__ __forceinline__ void issue_tile(uint32_t lds_stage, uint64_t kbase, u
     }
     dma_tile<kNT>(lds_stage, kbase, vbase, off);
   }
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  // gfx9 s_waitcnt encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt_hi[15:14]
-  constexpr int imm = (N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14);
-  __builtin_amdgcn_s_waitcnt(imm);
-}
-
-__device__ __forceinline__ void wait_lds() {
-  // lgkmcnt(0); vmcnt and expcnt left at their maxima
-  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
 }
 
 struct RowTile {
@@ -495,61 +459,6 @@ __device__ __forceinline__ void compute_tile(const TileFrags& f, const bf16x8 (*
 #undef ECHO_FENCE
 }
 
-// The wave's index in the workgroup, known to the compiler as wave-uniform (so
-// that everything derived from it stays in scalar registers).
-__device__ __forceinline__ int wave_id() {
-  return __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
-}
-
-struct MainArgs {
-  const uint16_t* q;
-  const uint16_t* k_new;
-  const uint16_t* v_new;
-  const uint16_t* k_cache;
-  const uint16_t* v_cache;
-  const int32_t* block_table;  // paged prefix (else nullptr): see KvSource
-  int page_shift;              // log2 of the page size (>= 5: a tile never straddles pages)
-  int max_pages;
-  const uint32_t* tree_mask;
-  int W, hq, hkv, G;
-  float scale2;
-  float* out;
-  float* lse;
-};
-
-// Unit descriptors are written by the plan launch and only read here: load
-// them through the constant address space (scalar loads when the index is
-// wave-uniform).
-typedef __attribute__((address_space(4))) const int32_t const_i32_t;
-__device__ __forceinline__ Unit load_unit(const Unit* units, int i) {
-  static_assert(sizeof(Unit) == 12 * sizeof(int32_t), "unit layout");
-  const_i32_t* p = (const_i32_t*)(units + i);
-  Unit u;
-  u.tile_start = p[0];
-  u.tile_end = p[1];
-  u.q0 = p[2];
-  u.nslots = p[3];
-  u.kb = p[4];
-  u.P = p[5];
-  u.ntail = p[6];
-  u.passes = p[7];
-  u.rpp = p[8];
-  u.group = p[9];
-  u.cut = p[10];
-  u.pad = p[11];
-  return u;
-}
-
-// A workgroup's start record, through the constant address space as the units.
-__device__ __forceinline__ WgStart load_wg_start(const WgStart* starts, int b) {
-  static_assert(sizeof(WgStart) == 16 * sizeof(int32_t), "start record layout");
-  const_i32_t* p = (const_i32_t*)(starts + b);
-  int32_t w[16];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) w[k] = p[k];
-  return __builtin_bit_cast(WgStart, w);
-}
-
 // Issue side of a wave's ring: the wave's k-th tile is lo + k; its copy goes to
 // stage k % 2 (nothing is copied where the wave's stream of the unit is empty).
 struct Issuer {
@@ -636,14 +545,6 @@ __device__ __forceinline__ void issue_next(Issuer& is, const MainArgs& a, const 
                         row_bytes, tn, cp);
   }
   ++is.k;
-}
-
-// The tree-mask word of tail tile lt for a row of slot `slot` (0 outside).
-__device__ __forceinline__ uint32_t mask_word(const MainArgs& a, const Unit& ud, bool row_ok,
-                                              int slot, int lt) {
-  return (row_ok && lt >= 0 && lt < ud.ntail && lt < a.W)
-             ? a.tree_mask[size_t(slot) * a.W + lt]
-             : 0u;
 }
 
 // Dims 16 (2j) + 4 g + [0, 4) and 16 (2j + 1) + 4 g + [0, 4) of a lane's row,
@@ -937,6 +838,7 @@ int32_t launch_attn_impl(const AttnArgs& a, bool plan, bool combine, hipStream_t
   const size_t ucap = unit_capacity(a.R, a.max_rows, a.hq, a.hkv);
   AttnWs ws = attn_layout(a.workspace, ucap, nb);
   const int G = a.hq / a.hkv;
+  const bool wide = attn_args_wide(a, nb);
   KvSource kv;
   kv.kv_offsets = a.kv_offsets;
   kv.kv_rows = static_cast<long long>(a.kv_rows);
@@ -958,7 +860,7 @@ int32_t launch_attn_impl(const AttnArgs& a, bool plan, bool combine, hipStream_t
                        dim3(kPageChunk), 0, stream, kv);
   }
   if (plan)
-    hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(kThreads),
+    hipLaunchKernelGGL(wide ? attn_plan_kernel<true> : attn_plan_kernel<false>, dim3(1), dim3(kThreads),
                        plan_table_words(a.R < kThreads ? a.R : kThreads) * sizeof(int32_t), stream,
                        a.q_offsets, kv, a.R, a.hkv, G, a.max_rows, nb,
                        static_cast<long long>(ucap), ws, a.status);
@@ -985,16 +887,18 @@ int32_t launch_attn_impl(const AttnArgs& a, bool plan, bool combine, hipStream_t
   // they still leave a few microseconds of idle time around the kernel, so a
   // step timed for throughput runs without them
   void* main_args[] = {&m, &ws};
-  if (hipExtLaunchKernel(reinterpret_cast<const void*>(&attn_main_kernel), dim3(unsigned(nb)),
-                         dim3(kWaves * kWave), main_args, 0, stream, a.ev_start, a.ev_stop,
-                         0) != hipSuccess)
+  const void* main_kernel = wide ? reinterpret_cast<const void*>(&attn_wide_kernel)
+                                 : reinterpret_cast<const void*>(&attn_main_kernel);
+  if (hipExtLaunchKernel(main_kernel, dim3(unsigned(nb)),
+                         dim3((wide ? kWideWaves : kWaves) * kWave), main_args, 0, stream,
+                         a.ev_start, a.ev_stop, 0) != hipSuccess)
     return ECHO_ERR_HIP;
   // cut units number fewer than the main kernel's workgroups
   if (combine) {
     const long long cache_rows = a.block_table == nullptr
                                      ? static_cast<long long>(a.kv_rows)
                                      : static_cast<long long>(a.num_pages) * a.page_size;
-    if (combine_rows_per_thread(a.R, a.max_rows, a.hq, a.hkv, nb, cache_rows) == 1)
+    if (combine_rows_per_thread(a.R, a.max_rows, a.hq, a.hkv, nb, cache_rows, wide) == 1)
       hipLaunchKernelGGL(attn_combine_kernel<1>, dim3(unsigned(nb * combine_blocks<1>())),
                          dim3(kThreads), 0, stream, a.hq, a.hkv, G, ws, a.out, a.lse);
     else

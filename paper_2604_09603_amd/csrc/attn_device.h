@@ -15,6 +15,7 @@ constexpr int kThreads = 256;       // plan / combine workgroups
 constexpr int kWaves = 4;           // main kernel: waves (streams) per workgroup, one per CU
 constexpr int kMaxMT = 4;           // 16-row tiles per stream (394 of the 512 registers a wave has)
 constexpr int kPassRows = kMaxMT * 16;  // rows per stream (64)
+constexpr int kWideRows = kWaves * kPassRows;  // wide units: rows of one KV head per unit (256)
 constexpr int kWaveStages = 2;      // per-wave LDS ring depth (32-key K+V tiles)
 constexpr int kTileKeys = 32;       // keys per tile
 constexpr int kMaskWords = 2;       // tree-tail mask words preloaded per row and segment
@@ -33,14 +34,16 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // One unit of the tile stream: a group of four streams of one request.
 // Stream s = 4 * group + w runs KV head s / passes over the rows of pass
-// s % passes; s >= hkv * passes is empty.
+// s % passes; s >= hkv * passes is empty.  A wide unit (see attn_is_wide) is one
+// KV head, group / passes, with the rows of pass group % passes, up to 256 of
+// them; its stream w is the w-th 64 of those rows.
 struct Unit {
   int32_t tile_start, tile_end;  // global tile range: ntail tail tiles, then prefix tiles
   int32_t q0, nslots;            // the request's verify slots
   int32_t kb, P;                 // KV prefix rows [kb, kb + P)
   int32_t ntail, passes;         // ceil(nslots / 32); row passes per KV head
   int32_t rpp, group;            // rows per pass (the last pass may have fewer); stream group
-  int32_t cut, pad;              // cut: covered by more than one workgroup
+  int32_t cut, wide;             // cut: covered by more than one workgroup
 };
 
 struct Cut {
@@ -58,7 +61,7 @@ struct WgStart {
 
 struct AttnWs {
   int32_t* meta;   // [0] units, [1] tiles, [2] cut units, [3] workgroups with work
-  Unit* units;
+  Unit* units;     // wide units: one record per request, of its group 0
   WgStart* wg_start;  // [nb], written for every workgroup by each plan
   Cut* cuts;
   // partials of the cut units: [2 * nb * 4 * 64][4] reference max (log2 units),
@@ -81,6 +84,45 @@ __host__ inline size_t unit_capacity(int R, int max_rows, int hq, int hkv) {
   const size_t passes = size_t(R) * size_t(fill_passes(hkv)) +
                         (size_t(max_rows) * (hq / hkv) + kPassRows - 1) / kPassRows;
   return size_t(R) + (size_t(hkv) * passes + kWaves - 1) / kWaves;
+}
+
+// Whether a launch runs wide units: one KV head and up to 256 rows per unit,
+// its tiles copied once into an LDS ring that eight waves of 32 rows share.
+// Ordinary units copy a head's tiles once per pass of 64 rows, and with fewer KV
+// heads than their four waves also once per wave.  Measured on single calls (us,
+// ordinary -> wide; rows: per KV head, the mean of max_rows / R slots):
+// * 128 rows and more: 125.9 -> 117.7 (64 / 4 heads, 16 requests of 8000 keys),
+//   180.7 -> 164.9 (128 / 8, 4 of 20,000), 45.7 -> 41.2 (64 / 1, 32 of 1000);
+//   below it, with four heads or more, even (148.3 -> 148.8, 64 / 8, 104 rows) or
+//   slower (91.6 -> 95.0, 64 / 4, 80 rows), so there the ordinary ones are kept;
+// * fewer rows over fewer than four heads: 80.4 -> 62.0 (8 / 1, 128 of 4000: 62
+//   tiles per workgroup), but 26.3 -> 29.3 (8 / 1, 32 of 1000: 4 tiles), where
+//   the ring's start-up shows: wide from 32 tiles per workgroup on.  Two heads fill an
+//   ordinary unit with two passes each and stay even (111.4 -> 110.3, 16 / 2, 24 rows;
+//   152.2 -> 155.9, 64 / 2, 96 rows): not wide.
+// kv_keys: the cached keys of all requests or an upper bound, prefix_cap: of one.
+// The 32-bit tile numbers must hold every request at the longest prefix whatever
+// the slots' spread; beyond that the ordinary units, with fewer tiles, are kept.
+__host__ inline bool attn_is_wide(int R, int max_rows, int hq, int hkv, long long prefix_cap,
+                                  long long kv_keys, int nb) {
+  if (R <= 0 || hkv <= 0) return false;
+  const long long G = hq / hkv;
+  const long long mean = (long long)(max_rows / R) * G;
+  if (hkv >= 1 << 15) return false;  // (24-bit products in the copies' addresses)
+  if (mean < 2 * kPassRows &&
+      (hkv >= kWaves || hkv == 2 || kv_keys / kTileKeys * hkv < 32ll * nb))
+    return false;
+  const long long passes = ((long long)max_rows * G + kWideRows - 1) / kWideRows + R;
+  const long long tiles = prefix_cap / kTileKeys + max_rows / kTileKeys + 2;
+  return tiles < (1ll << 29) / (passes * hkv);
+}
+
+__host__ inline bool attn_args_wide(const AttnArgs& a, int nb) {
+  const long long rows = a.kv_rows;
+  if (a.block_table == nullptr) return attn_is_wide(a.R, a.max_rows, a.hq, a.hkv, rows, rows, nb);
+  const long long cap = (long long)a.max_pages * a.page_size;
+  const long long pool = (long long)a.num_pages * a.page_size;
+  return attn_is_wide(a.R, a.max_rows, a.hq, a.hkv, cap, pool < cap * a.R ? pool : cap * a.R, nb);
 }
 
 __host__ __device__ inline size_t part_rows(int nb) {
@@ -148,6 +190,14 @@ struct Stream {
 
 __device__ __forceinline__ Stream stream_of(const Unit& u, int w, int hkv, int G) {
   Stream s = {0, 0, 0};
+  if (u.wide) {
+    if (u.passes <= 0) return s;
+    const int pass0 = (u.group % u.passes) * u.rpp;
+    s.kvh = u.group / u.passes;
+    s.row0 = pass0 + w * kPassRows;
+    s.rows = max(0, min(kPassRows, min(u.rpp, u.nslots * G - pass0) - w * kPassRows));
+    return s;
+  }
   const int id = kWaves * u.group + w;
   if (u.passes <= 0 || id >= hkv * u.passes) return s;
   s.kvh = id / u.passes;
@@ -206,6 +256,12 @@ __device__ __forceinline__ bool request_ok(const RequestIn& in, const KvSource& 
   return in.P >= 0 && in.P <= (long long)kv.max_pages * kv.page_size;
 }
 
+// Row passes of an ordinary unit's heads (see request_shape).
+__device__ __forceinline__ int ordinary_passes(int rows, int hkv) {
+  const int p = (rows + kPassRows - 1) / kPassRows;
+  return p == 0 ? 0 : max(p, min(rows, fill_passes(hkv)));
+}
+
 struct RequestShape {
   int groups, tiles, q0, nsl, kb, P, ntail, passes, rpp;
 };
@@ -218,37 +274,39 @@ struct RequestShape {
 // head's tiles and share them in the caches.
 // `ok` is request_ok of request r (evaluated once per plan).  A paged request's
 // kb is its index (its block table row), a contiguous one's its first row.
+template <bool kWide>
 __device__ __forceinline__ RequestShape request_shape(const RequestIn& in, const KvSource& kv,
                                                       bool ok, int R, int hkv, int G, int r) {
-  RequestShape s = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  RequestShape s = {};
   if (r >= R || !ok) return s;
   s.q0 = in.q0;
   s.nsl = in.q1 - in.q0;
   s.kb = kv.block_table == nullptr ? int(in.k0) : r;
   s.P = int(in.P);
   const int rows = s.nsl * G;
-  s.passes = (rows + kPassRows - 1) / kPassRows;
+  s.passes = kWide ? (rows + kWideRows - 1) / kWideRows : ordinary_passes(rows, hkv);
   if (s.passes == 0) return s;
-  s.passes = max(s.passes, min(rows, fill_passes(hkv)));
   s.rpp = (rows + s.passes - 1) / s.passes;
   s.ntail = (s.nsl + kTileKeys - 1) / kTileKeys;
-  s.groups = (hkv * s.passes + kWaves - 1) / kWaves;
+  s.groups = kWide ? hkv * s.passes : (hkv * s.passes + kWaves - 1) / kWaves;
   s.tiles = s.ntail + (s.P + kTileKeys - 1) / kTileKeys;
   return s;
 }
 
 // request_shape of request r, its fields loaded here (r < R).
+template <bool kWide>
 __device__ __forceinline__ RequestShape request_shape_at(const int32_t* q_offsets,
                                                          const KvSource& kv, bool ok, int R,
                                                          int hkv, int G, int r) {
-  if (r >= R || !ok) return RequestShape{0, 0, 0, 0, 0, 0, 0, 0, 0};
-  return request_shape(load_request(q_offsets, kv, r), kv, ok, R, hkv, G, r);
+  if (r >= R || !ok) return RequestShape{};
+  return request_shape<kWide>(load_request(q_offsets, kv, r), kv, ok, R, hkv, G, r);
 }
 
 // Unit g of a request of shape s whose tiles start at tile tb; b0 and b1: the
 // workgroups whose ranges hold its first and its last tile.
-__device__ __forceinline__ Unit make_unit(const RequestShape& s, int tb, int g, long long T, int nw,
-                                          const DivBy& by_t, int& b0, int& b1) {
+__device__ __forceinline__ Unit make_unit(const RequestShape& s, int tb, int g, bool wide,
+                                          long long T, int nw, const DivBy& by_t, int& b0,
+                                          int& b1) {
   Unit u;
   u.tile_start = tb + g * s.tiles;
   u.tile_end = u.tile_start + s.tiles;
@@ -263,7 +321,7 @@ __device__ __forceinline__ Unit make_unit(const RequestShape& s, int tb, int g, 
   b0 = range_of(u.tile_start, T, nw, by_t);
   b1 = range_of(u.tile_end - 1, T, nw, by_t);
   u.cut = b0 != b1;
-  u.pad = 0;
+  u.wide = wide ? 1 : 0;
   return u;
 }
 
@@ -282,7 +340,7 @@ __host__ __device__ inline size_t plan_table_words(int R) {
 //   first tile writes that range's record.
 // * `pre` (may be null): request threadIdx.x's fields as load_request gives
 //   them, already in hand (R <= NT).
-template <int NT>
+template <int NT, bool kWide>
 __device__ void plan_body(const int32_t* __restrict__ q_offsets, const KvSource& kv, int R, int hkv,
                           int G, int max_rows, int nb, long long ucap, const AttnWs& ws,
                           int32_t* status, int32_t* tables = nullptr,
@@ -295,7 +353,7 @@ __device__ void plan_body(const int32_t* __restrict__ q_offsets, const KvSource&
   // are computed once and kept for pass B; the shape is taken with the same
   // loads as the validity check
   const bool single = R <= NT;
-  RequestShape s1 = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  RequestShape s1 = {};
   int ub1 = 0, tb1 = 0;
   int bits = 0;
   for (int r = tid; r < R; r += NT) {
@@ -305,18 +363,24 @@ __device__ void plan_body(const int32_t* __restrict__ q_offsets, const KvSource&
       for (int c = 0; c < kv.page_chunks; ++c) ok = ok && kv.page_bad[size_t(r) * kv.page_chunks + c] == 0;
     s_ok[r] = ok ? 1 : 0;
     if (!ok) bits |= ECHO_DATA_BAD_OFFSETS;
-    if (single) s1 = request_shape(in, kv, ok, R, hkv, G, r);
+    if (single) s1 = request_shape<kWide>(in, kv, ok, R, hkv, G, r);
   }
   __syncthreads();
   auto ok_of = [&](int r) { return r < R && s_ok[r] != 0; };
 
+  // the units an ordinary split would need: what the capacity check counts for
+  // either split (a wide one keeps one record per request)
+  auto need = [&](const RequestShape& s) {
+    return kWide ? (hkv * ordinary_passes(s.nsl * G, hkv) + kWaves - 1) / kWaves : s.groups;
+  };
   // pass A: total units and tiles
   long long T = 0, U = 0;
   for (int base = 0; base < R; base += NT) {
     const RequestShape s =
-        single ? s1 : request_shape_at(q_offsets, kv, ok_of(base + tid), R, hkv, G, base + tid);
+        single ? s1
+               : request_shape_at<kWide>(q_offsets, kv, ok_of(base + tid), R, hkv, G, base + tid);
     int tot_u, tot_t;
-    const int2 ex = block_exclusive_sum2<NT>(make_int2(s.groups, s.groups * s.tiles), s_scan2,
+    const int2 ex = block_exclusive_sum2<NT>(make_int2(need(s), s.groups * s.tiles), s_scan2,
                                                    &tot_u, &tot_t);
     if (single) {
       s1 = s;
@@ -348,6 +412,7 @@ __device__ void plan_body(const int32_t* __restrict__ q_offsets, const KvSource&
   // pass B: units, the cut units and each workgroup's start record
   const DivBy by_t(T > 0 ? T : 1), by_nw(nw > 0 ? nw : 1);
   const bool by_wg = single && tables != nullptr;
+  const int records = kWide ? R : int(U);  // entries of ws.units
   int32_t* s_tb = tables;             // R + 1: first tile of each request's units, then T
   int32_t* s_ub = tables + (R + 1);   // R: first unit of each request
   RequestShape* s_sh = reinterpret_cast<RequestShape*>(tables + 2 * (R + 1));  // R
@@ -362,8 +427,8 @@ __device__ void plan_body(const int32_t* __restrict__ q_offsets, const KvSource&
       tot_u = int(U);
       tot_t = int(T);
     } else {
-      s = request_shape_at(q_offsets, kv, ok_of(base + tid), R, hkv, G, base + tid);
-      const int2 ex = block_exclusive_sum2<NT>(make_int2(s.groups, s.groups * s.tiles),
+      s = request_shape_at<kWide>(q_offsets, kv, ok_of(base + tid), R, hkv, G, base + tid);
+      const int2 ex = block_exclusive_sum2<NT>(make_int2(need(s), s.groups * s.tiles),
                                                      s_scan2, &tot_u, &tot_t);
       ub = unit_run + ex.x;
       tb = tile_run + ex.y;
@@ -383,13 +448,18 @@ __device__ void plan_body(const int32_t* __restrict__ q_offsets, const KvSource&
     }
     if (by_wg && tid == 0) s_tb[R] = int(T);
     int c = cb;
+    if (kWide && base + tid < R) {
+      int b0, b1;
+      ws.units[base + tid] = make_unit(s, tb, 0, kWide, T, nw, by_t, b0, b1);
+    }
     for (int g = 0; g < s.groups; ++g) {
       int b0, b1;
-      const Unit u = make_unit(s, tb, g, T, nw, by_t, b0, b1);
-      ws.units[ub + g] = u;
+      const Unit u = make_unit(s, tb, g, kWide, T, nw, by_t, b0, b1);
+      const int rec = kWide ? base + tid : ub + g;
+      if (!kWide) ws.units[rec] = u;
       if (u.cut) {
         Cut cu;
-        cu.unit = ub + g;
+        cu.unit = rec;
         cu.b0 = b0;
         cu.b1 = b1;
         cu.first_slot = range_lo(T, b0, by_nw) < u.tile_start ? 1 : 0;
@@ -409,8 +479,8 @@ __device__ void plan_body(const int32_t* __restrict__ q_offsets, const KvSource&
         WgStart st;
         st.lo = int(blo);
         st.hi = int(bhi);
-        st.nunits = int(U);
-        st.first_unit = ub + g;
+        st.nunits = records;
+        st.first_unit = rec;
         st.u = u;
         ws.wg_start[b] = st;
         blo = bhi;
@@ -434,14 +504,14 @@ __device__ void plan_body(const int32_t* __restrict__ q_offsets, const KvSource&
       WgStart st;
       st.lo = blo;
       st.hi = int(range_lo(T, b + 1, by_nw));
-      st.nunits = int(U);
-      st.first_unit = s_ub[r] + g;
-      st.u = make_unit(s, s_tb[r], g, T, nw, by_t, b0, b1);
+      st.nunits = records;
+      st.first_unit = kWide ? r : s_ub[r] + g;
+      st.u = make_unit(s, s_tb[r], g, kWide, T, nw, by_t, b0, b1);
       ws.wg_start[b] = st;
     }
   }
   if (tid == 0) {
-    ws.meta[0] = unit_run;
+    ws.meta[0] = records;
     ws.meta[1] = int(T);
     ws.meta[2] = cut_run;
     ws.meta[3] = nw;
@@ -469,9 +539,13 @@ constexpr int kFastParts = 4;  // cuts over at most this many workgroups merge i
 // bound of the prefixes) most of the grid has no cut to merge, and the smaller
 // grid of two rows per thread is kept.
 __host__ inline int combine_rows_per_thread(int R, int max_rows, int hq, int hkv, int nb,
-                                            long long kv_rows) {
+                                            long long kv_rows, bool wide) {
   if (R <= 0 || hkv <= 0) return 2;
   const int rows = (max_rows / R) * (hq / hkv);
+  if (wide) {
+    const long long units = (long long)R * hkv * ((rows + kWideRows - 1) / kWideRows);
+    return units * 3 <= nb ? 1 : 2;
+  }
   int passes = (rows + kPassRows - 1) / kPassRows;
   passes = passes > 0 ? passes : 1;
   const int fill = fill_passes(hkv) < rows ? fill_passes(hkv) : rows;

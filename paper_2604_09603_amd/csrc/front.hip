@@ -54,7 +54,7 @@ struct FrontArgs {
   int32_t* status;
 };
 
-template <bool kAligned>
+template <bool kAligned, bool kWide>
 __global__ __launch_bounds__(kFrontThreads) void front_kernel(FrontArgs a) {
   extern __shared__ int32_t smem[];
   // The request tables of flatten & pack are loaded first, into registers, so
@@ -89,8 +89,8 @@ __global__ __launch_bounds__(kFrontThreads) void front_kernel(FrontArgs a) {
   in.P = k1 - k0;
   // (the tables reuse the LDS of the phases before; every thread has read its
   // slot offsets before the plan's first barrier)
-  plan_body<kFrontThreads>(a.q_offsets, a.kv, a.R, a.hkv, a.G, a.max_rows, a.nb, a.ucap, a.aws,
-                           a.status, smem, pre ? &in : nullptr);
+  plan_body<kFrontThreads, kWide>(a.q_offsets, a.kv, a.R, a.hkv, a.G, a.max_rows, a.nb, a.ucap,
+                                  a.aws, a.status, smem, pre ? &in : nullptr);
 }
 
 }  // namespace
@@ -142,7 +142,9 @@ int32_t launch_front(const FrontLaunch& f, hipStream_t stream) {
   a.status = f.status;
   const size_t lds = front_lds_bytes(f.R, f.budget);
   const bool aligned = (reinterpret_cast<uintptr_t>(f.selected) & 15u) == 0;
-  auto kern = aligned ? front_kernel<true> : front_kernel<false>;
+  const bool wide = attn_is_wide(f.R, f.max_rows, f.hq, f.hkv, a.kv.kv_rows, a.kv.kv_rows, a.nb);
+  auto kern = aligned ? (wide ? front_kernel<true, true> : front_kernel<true, false>)
+                      : (wide ? front_kernel<false, true> : front_kernel<false, false>);
   if (lds > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)

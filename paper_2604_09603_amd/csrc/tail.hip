@@ -80,7 +80,7 @@ int32_t launch_tail(const AttnArgs& a, const int32_t* slot_parent, const int32_t
   const long long cache_rows = a.block_table == nullptr
                                    ? static_cast<long long>(a.kv_rows)
                                    : static_cast<long long>(a.num_pages) * a.page_size;
-  if (combine_rows_per_thread(a.R, a.max_rows, a.hq, a.hkv, nb, cache_rows) == 1)
+  if (combine_rows_per_thread(a.R, a.max_rows, a.hq, a.hkv, nb, cache_rows, attn_args_wide(a, nb)) == 1)
     hipLaunchKernelGGL(tail_kernel<1>, dim3(unsigned(t.nacc + nb * combine_blocks<1>())),
                        dim3(kThreads), 0, stream, t);
   else

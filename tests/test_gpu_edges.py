@@ -316,6 +316,40 @@ def test_head_layouts_every_row(hq, hkv):
     _check_all(b)
 
 
+@pytest.mark.parametrize("hq,hkv,page_size", [(64, 4, 32), (40, 5, 64), (24, 1, 128)])
+def test_wide_units_every_row(hq, hkv, page_size):
+    """Batches whose mean rows per KV head select the shared-ring kernel: requests of
+    8 Hq/Hkv rows and more next to requests with fewer rows than a wave has, row
+    counts on both sides of its 32-row blocks, of the 128 rows up to which two waves
+    share the keys, and of the 256 rows of a pass, more than 64 slots in a tail
+    (mask words past the preloaded ones), and prefixes on both sides of a tile and
+    of a pair of tiles.  Every row against the oracle; the paged path bit for bit."""
+    from tests.test_gpu_serve import run_paged, to_pages
+    rng = np.random.default_rng(hq + 7 * hkv)
+    sizes = [0, 1, 3, 7, 8, 15, 16, 17, 31, 40, 70, 12]
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    parent = np.concatenate([np.maximum((np.arange(n) - 1) // 3, -1) for n in sizes])
+    N = int(offs[-1])
+    pool = dict(cand_offsets=offs, parent=parent.astype(np.int32),
+                token=rng.integers(0, 4, N).astype(np.int32),
+                logq=rng.uniform(-0.5, 0.0, N).astype(np.float32),
+                root_token=rng.integers(0, 4, len(sizes)).astype(np.int32))
+    b = make_micro_batch(pool, N, hq=hq, hkv=hkv, p_range=(0, 1), seed=hq)
+    P = np.array([0, 1, 31, 32, 33, 64, 65, 95, 96, 300, 17, 700], np.int32)
+    b["prefix_len"] = P
+    b["kv_offsets"] = np.concatenate([[0], np.cumsum(P.astype(np.int64))])
+    T = int(P.sum())
+    b["k_cache"], b["v_cache"] = _bf16(rng, T, hkv, 128, scale=2.0), _bf16(rng, T, hkv, 128)
+    res, ref = _check_all(b)
+    m = ref["mask"]
+    kp, vp, bt, plen = to_pages(b["k_cache"], b["v_cache"], b["kv_offsets"], page_size, rng)
+    out, lse, status = run_paged(b, m, kp, vp, bt, plen, page_size)
+    nq = m["num_slots"]
+    assert status == 0
+    assert np.array_equal(out[:nq].view(np.uint32), res["out"][:nq].view(np.uint32))
+    assert np.array_equal(lse[:nq].view(np.uint32), res["lse"][:nq].view(np.uint32))
+
+
 def _check_mask_only(b, offset):
     """echo_build_tree_mask on the oracle's selection stored `offset` bytes past a
     16-byte boundary: every output equal to the oracle's."""
