@@ -320,11 +320,11 @@ int32_t echo_accept(const int32_t* q_offsets, const int32_t* slot_parent,
  * echo_accept on one stream, with the same arguments (in that order; the
  * mask's unused workspace is dropped, `token` is the mask's candidate tokens,
  * `max_rows` serves the attention and the acceptance) and bit-identical
- * outputs and status bits.  It runs the gate's last phase, flatten & pack and
- * the attention's plan in one single-workgroup launch (the three are one
- * workgroup each and run back to back), and the acceptance inside the
- * attention's combine launch (it reads nothing the attention writes): five
- * launches instead of eight.  Every check of the four calls runs before
+ * outputs and status bits.  It runs the end of the gate, flatten & pack and
+ * the attention's plan in one launch (the whole gate too, for a small pool of
+ * candidates), and the acceptance inside the attention's combine launch (it
+ * reads nothing the attention writes): three to five launches instead of
+ * eight.  Every check of the four calls runs before
  * anything is launched; a failing check launches nothing.
  * Needs mask_words * 32 >= budget + 1 and the same LDS bound as the mask
  * call (ECHO_ERR_UNSUPPORTED beyond it).

@@ -394,16 +394,23 @@ int32_t echo_verify_step(
   if (!accept_len || !accept_slots || !bonus_token) return ECHO_ERR_INVALID_ARG;
   if (max_rows > 0 && !target_token) return ECHO_ERR_INVALID_ARG;
   hipStream_t s = as_stream(stream);
-  rc = echo::launch_gate_select_only(cand_offsets, parent, logq, R, N, budget, path_score,
-                                     selected, num_selected, gate_workspace, status, s);
-  if (rc != ECHO_OK) return rc;
+  const int list = echo::front_gate_list(N, R, budget);
+  if (list >= 0) {
+    rc = echo::launch_gate_select_only(cand_offsets, parent, logq, R, N, budget, path_score,
+                                       selected, num_selected, gate_workspace, status, list != 0,
+                                       s);
+    if (rc != ECHO_OK) return rc;
+  }
   echo::FrontLaunch f;
   f.N = N;
   f.R = R;
   f.budget = budget;
   f.mask_words = mask_words;
   f.gate_workspace = gate_workspace;
+  f.logq = logq;
+  f.path_score = path_score;
   f.selected = selected;
+  f.num_selected = num_selected;
   f.cand_offsets = cand_offsets;
   f.parent = parent;
   f.token = token;

@@ -94,6 +94,12 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
   return uint32_t(__builtin_amdgcn_readlane(int(wave_scan(v, 0u, MaxOp{})), kWave - 1));
 }
 
+// Position of this lane among the lanes of `bal` below it.
+__device__ __forceinline__ int lanes_below(uint64_t bal) {
+  return int(__builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32),
+                                       __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u)));
+}
+
 // Exclusive prefix sum over a whole block of NT threads; *total receives the
 // block sum.  `scratch` must hold NT/64 + 1 ints of shared memory.  Each wave
 // scans its lanes, then every wave scans the wave totals for itself.  Contains

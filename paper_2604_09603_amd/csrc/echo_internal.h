@@ -16,11 +16,11 @@ int32_t launch_gate(const int32_t* cand_offsets, const int32_t* parent, const fl
                     hipStream_t stream);
 size_t gate_workspace_bytes(int32_t R, int32_t N, int32_t budget);
 // The top-B gate without its last phase (gate_finish), which the fused step's
-// front kernel runs.
+// front kernel runs; list: gate_select leaves the selection's candidates in order.
 int32_t launch_gate_select_only(const int32_t* cand_offsets, const int32_t* parent,
                                 const float* logq, int32_t R, int32_t N, int32_t budget,
                                 float* path_score, uint8_t* selected, int32_t* num_selected,
-                                void* workspace, int32_t* status, hipStream_t stream);
+                                void* workspace, int32_t* status, bool list, hipStream_t stream);
 
 // Path scores only (the first gate launch): per candidate the orderable key
 // (0 = never selectable), the clamped parent as a global index (-1: child of
@@ -113,13 +113,16 @@ int32_t launch_commit_kv(const int32_t* q_offsets, const int32_t* accept_len,
 
 int device_cu_count();
 
-// Fused step (front.hip): the gate's last phase, flatten & pack and the
-// attention plan (contiguous cache) in one single-workgroup launch, after
-// launch_gate_select_only and before launch_tree_verify_attn_main.
+// Fused step (front.hip): the end of the gate, flatten & pack and the attention plan
+// (contiguous cache) in one launch, after launch_gate_select_only (unless
+// front_gate_list is negative) and before launch_tree_verify_attn_main.
 struct FrontLaunch {
   int32_t N, R, budget, mask_words;
   void* gate_workspace;
+  const float* logq;
+  float* path_score;
   uint8_t* selected;
+  int32_t* num_selected;
   const int32_t* cand_offsets;
   const int32_t* parent;
   const int32_t* token;
@@ -137,7 +140,9 @@ struct FrontLaunch {
   void* attn_workspace;
   int32_t* status;
 };
-size_t front_lds_bytes(int32_t R, int32_t budget);
+// What the front kernel wants of launch_gate_select_only: its `list` argument, or
+// -1 if it runs the whole gate itself.
+int front_gate_list(int32_t N, int32_t R, int32_t budget);
 int32_t launch_front(const FrontLaunch& f, hipStream_t stream);
 
 // Fused step (tail.hip): the attention's combine and the greedy acceptance in

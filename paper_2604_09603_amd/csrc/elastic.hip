@@ -110,12 +110,6 @@ __device__ __forceinline__ uint64_t rank_word(uint32_t key, int i) {
   return (uint64_t(key) << 32) | uint64_t(0xFFFFFFFFu - uint32_t(i));
 }
 
-// Position of this lane among the lanes of `bal` below it.
-__device__ __forceinline__ int lanes_below(uint64_t bal) {
-  return int(__builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32),
-                                       __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u)));
-}
-
 // counter[d] += 1 for every lane with `on` and depth d, with one LDS atomic per
 // distinct depth in the wave; returns the counter's value before this lane's
 // increment (lanes of one depth take consecutive values).  Every lane of the

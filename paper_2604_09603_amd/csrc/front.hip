@@ -1,15 +1,23 @@
-// The fused step's front kernel: the last phase of the top-B gate (eq. 4),
-// flatten & pack (Fig. 3, stage 3) and the attention plan, one after another
-// on one workgroup.  Each of the three is one workgroup that waits for the one
-// before it, so as separate launches the step pays a kernel boundary (one
-// kernel's drain, the next one's launch) between each pair.
+// The fused step's front kernel: the end of the top-B gate (eq. 4), flatten & pack
+// (Fig. 3, stage 3) and the attention plan in one launch of two workgroups.  All
+// three are chains of one workgroup's round trips and barriers, and the plan needs
+// of flatten & pack only the slot offsets: both workgroups find the selection and
+// the slot offsets for themselves (the same values, from the same inputs), then
+// workgroup 0 packs the slots and masks while workgroup 1 makes the plan.  Only
+// workgroup 0 writes what is not also computed by the other; the slot offsets are
+// written by both, with the same values.  At 90,880 candidates and 128 requests the
+// kernel went from 21.3 to 15.3 us, at 208 and 4 requests this kernel and the two
+// gate launches before it from 20.4 (and two launch gaps) to 14.0.
 //
-// The three phases share one dynamic LDS buffer: the gate's gathered
-// candidates (2 x 32 KB and the select blocks' offsets) first, then the mask's
-// request tables, compacted list and ancestor slots.  A barrier separates the
-// phases; the selection flags and slot offsets pass through global memory,
-// where the workgroup's own stores before a barrier are seen by its loads
-// after it.
+// The selection comes in one of three ways (see front_mode):
+//   small pool   no gate launch at all: the path scores, the threshold and the
+//                selection in LDS;
+//   lists        gate_select left the candidates of the threshold bin and above in
+//                index order: gathered, decided and compacted in LDS, where reading
+//                the flags of all N candidates back had cost two phases of their own
+//                (4.8 of 20 us at 90,880 candidates);
+//   flags        (a budget too large for that LDS, or more such candidates than it
+//                takes) the gate's last phase, then the flags.
 #include "attn_device.h"
 #include "echo_device.h"
 #include "echo_internal.h"
@@ -27,11 +35,22 @@ static_assert(kGateThreads == kFrontThreads && kMaskThreads == kFrontThreads,
 // kGateThreads + 1 offsets of the select blocks.
 constexpr size_t kFinishLds = size_t(2 * kSortCap + kGateThreads + 1) * sizeof(int32_t);
 
+constexpr int kModeFlags = 0, kModeLists = 1, kModeSmall = 2;
+// Candidates of a small pool, kSmallPer per thread.  Whole steps over N candidates
+// (8 / 8 heads, 64 keys), lists -> small pool: 28.5 -> 23.3 us at 208, 32.1 -> 28.6
+// at 2080, 36.6 -> 34.7 at 3120, 38.7 -> 38.4 at 4160, 42.0 -> 44.7 at 6136 (one
+// workgroup's searches and histogram rounds grow with N).
+constexpr int kSmallPer = 3;
+constexpr int kSmallPool = kSmallPer * kFrontThreads;
+
 struct FrontArgs {
-  // gate, last phase
+  // gate
   int N, nblocks;
   GateWs gws;
   uint8_t* selected;
+  const float* logq;      // small pool
+  float* path_score;      // small pool (nullable)
+  int32_t* num_selected;  // small pool
   // flatten & pack
   const int32_t* cand_offsets;
   const int32_t* parent;
@@ -54,33 +73,224 @@ struct FrontArgs {
   int32_t* status;
 };
 
-template <bool kAligned, bool kWide>
+__host__ __device__ inline size_t mask_region(int32_t R, int32_t budget) {
+  return (mask_words_bytes(R, budget) + 15) / 16 * 16;
+}
+
+// The selection from gate_select's lists into comp; its size, or -1 if the lists
+// do not fit (nothing is written then).
+__device__ int select_from_lists(const FrontArgs& a, bool first, int32_t* smem, int32_t* comp,
+                                 uint32_t* s_cnt) {
+  __shared__ int s_scan[kGateThreads / kWave + 1];
+  __shared__ RadixLds s_rl;
+  uint32_t* s_k = reinterpret_cast<uint32_t*>(smem);
+  int32_t* s_g = smem + kSortCap;
+  int* s_base = smem + 2 * kSortCap;
+  const int tid = threadIdx.x;
+  const int c = tid < a.nblocks ? int(a.gws.ccount[tid]) : 0;
+  const GateMeta mt = *a.gws.meta;
+  if (mt.num_selected == 0) return 0;
+  if (a.nblocks > kGateThreads) return -1;
+  for (int i = tid; i < 512; i += kGateThreads) (&s_rl.h[0][0])[i] = 0u;
+  int n;
+  const int ex = block_exclusive_sum<kGateThreads>(c, s_scan, &n);
+  if (n > kSortCap) return -1;
+  if (tid < a.nblocks) s_base[tid] = ex;
+  if (tid == 0) s_base[a.nblocks] = n;
+  __syncthreads();
+  for (int i = tid; i < n; i += kGateThreads) {
+    const int b = upper_bound_idx(s_base, a.nblocks + 1, i);
+    const uint2 e = a.gws.cand[size_t(b) * kGateThreads + (i - s_base[b])];
+    s_k[i] = e.x;
+    s_g[i] = int32_t(e.y);
+  }
+  __syncthreads();
+  uint32_t tk;
+  int32_t tg;
+  find_threshold(mt, n, a.N, [&](int i) { return s_k[i]; }, [&](int i) { return s_g[i]; }, s_rl,
+                 &tk, &tg);
+  const auto sel = [&](int i) {
+    const uint32_t k = s_k[i];
+    const bool in = k > tk || (k == tk && s_g[i] <= tg);
+    // (gate_select wrote the flags of the bins above)
+    if (first && (k >> kHistShift) == mt.bin) a.selected[s_g[i]] = in ? 1 : 0;
+    return in;
+  };
+  return compact_entries(n, sel, [&](int i) { return s_g[i]; }, comp, a.budget, s_cnt);
+}
+
+// A small pool's candidates in registers, loaded before anything waits.
+struct SmallPool {
+  int32_t par[kSmallPer];
+  float lq[kSmallPer];
+};
+
+__device__ __forceinline__ SmallPool load_small(const FrontArgs& a) {
+  SmallPool p;
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int g = k * kFrontThreads + int(threadIdx.x);
+    p.par[k] = g < a.N ? a.parent[g] : -1;
+    p.lq[k] = g < a.N ? a.logq[g] : 0.0f;
+  }
+  return p;
+}
+
+// The whole top-B gate of a small pool into comp; the selection's size.  offs: the
+// candidate offsets in LDS, ok: they are well formed.
+__device__ int select_small(const FrontArgs& a, const SmallPool& in, const int32_t* offs, bool ok,
+                            bool first, int32_t* smem, int32_t* comp, uint32_t* s_cnt, int* bits) {
+  __shared__ RadixLds s_rl;
+  __shared__ uint32_t s_fin[kGateThreads / kWave];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  // Scores top-down, all nodes of a depth in one round: (score, depth) of every node
+  // whose score is known, a NaN score where it is not.  A node folds the same
+  // binary32 adds in the same order as a walk from the root.  (Short code: with the
+  // instruction cache cold, an unrolled walk per node cost more than the launches
+  // it saved.)
+  uint2* s_node = reinterpret_cast<uint2*>(smem);
+  uint32_t* s_key = reinterpret_cast<uint32_t*>(smem);  // replaces them
+  constexpr uint32_t kUnknown = 0x7FFFFFFFu;
+  const int n = a.N;
+  int par[kSmallPer];
+  float lq[kSmallPer], sc[kSmallPer];
+  uint32_t open = 0u;  // bit k: the thread's node k has no score yet
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int g = k * kFrontThreads + tid;
+    sc[k] = -__builtin_inff();
+    lq[k] = in.lq[k];
+    par[k] = -1;
+    if (!ok || g >= n) continue;
+    const int lo = offs[upper_bound_idx(offs, a.R + 1, g)];
+    int p = in.par[k];
+    if (p < -1 || p >= g - lo) { *bits |= ECHO_DATA_BAD_PARENT; p = -1; }
+    if (lq[k] != lq[k]) { *bits |= ECHO_DATA_NAN_LOGQ; lq[k] = -__builtin_inff(); }
+    else if (lq[k] > 0.0f) { *bits |= ECHO_DATA_POS_LOGQ; lq[k] = 0.0f; }
+    if (p < 0) {
+      sc[k] = 0.0f + lq[k];
+      s_node[g] = make_uint2(__float_as_uint(sc[k]), 1u);
+    } else {
+      par[k] = lo + p;
+      open |= 1u << k;
+      s_node[g] = make_uint2(kUnknown, 0u);
+    }
+  }
+  for (int i = tid; i < 512; i += kGateThreads) (&s_rl.h[0][0])[i] = 0u;
+  // after ECHO_MAX_DEPTH - 1 rounds every node of depth <= ECHO_MAX_DEPTH is known
+  for (int round = 1; round < ECHO_MAX_DEPTH; ++round) {
+    if (!__syncthreads_or(open != 0u)) break;
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k) {
+      if (!((open >> k) & 1u)) continue;
+      const uint2 v = s_node[par[k]];
+      if (v.x == kUnknown || v.y >= ECHO_MAX_DEPTH) continue;
+      sc[k] = __uint_as_float(v.x) + lq[k];
+      s_node[k * kFrontThreads + tid] = make_uint2(__float_as_uint(sc[k]), v.y + 1u);
+      open &= ~(1u << k);
+    }
+  }
+  if (open != 0u) *bits |= ECHO_DATA_TOO_DEEP;  // deeper: their scores stay -inf
+  uint32_t key[kSmallPer];
+  uint32_t fin = 0u;
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int g = k * kFrontThreads + tid;
+    key[k] = score_key(sc[k]);
+    if (first && g < n && a.path_score != nullptr) a.path_score[g] = sc[k];
+    fin += uint32_t(__popcll(__ballot(key[k] != 0u)));
+  }
+  if (lane == 0) s_fin[tid / kWave] = fin;
+  __syncthreads();  // every score has been read
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int g = k * kFrontThreads + tid;
+    if (g < n) s_key[g] = key[k];
+  }
+  fin = 0u;
+#pragma unroll
+  for (int w = 0; w < kGateThreads / kWave; ++w) fin += s_fin[w];
+  const uint32_t m = min(uint32_t(a.budget), fin);
+  if (first && tid == 0) *a.num_selected = int32_t(m);
+  __syncthreads();
+  uint32_t tk = 0xFFFFFFFFu;
+  int32_t tg = -1;
+  if (m != 0u)
+    find_threshold(RadixSel{0u, 32, m, fin}, n, n, [&](int i) { return s_key[i]; },
+                   [](int i) { return int32_t(i); }, s_rl, &tk, &tg);
+  const auto sel = [&](int i) {
+    const uint32_t k = s_key[i];
+    const bool on = m != 0u && k != 0u && (k > tk || (k == tk && i <= tg));
+    if (first) a.selected[i] = on ? 1 : 0;
+    return on;
+  };
+  return compact_entries(n, sel, [](int i) { return int32_t(i); }, comp, a.budget, s_cnt);
+}
+
+template <bool kAligned, bool kWide, int kMode>
 __global__ __launch_bounds__(kFrontThreads) void front_kernel(FrontArgs a) {
-  extern __shared__ int32_t smem[];
+  extern __shared__ __attribute__((aligned(16))) int32_t smem[];
+  __shared__ uint32_t s_cnt[2 * kWave];
   // The request tables of flatten & pack are loaded first, into registers, so
   // that their memory latency passes with that of the gate's first loads.
   const MaskTables tab = load_mask_tables(a.cand_offsets, a.root_token, a.prefix_len, a.R);
   // and the plan's KV offsets (one request per thread), which no phase before
   // it writes
   const int tid = threadIdx.x;
-  const bool pre = a.plan && a.R <= kFrontThreads;
+  const bool first = blockIdx.x == 0;  // packs; the other one plans
+  const bool pre = !first && a.R <= kFrontThreads;
   long long k0 = 0, k1 = 0;
   if (pre && tid < a.R) {
     k0 = a.kv.kv_offsets[tid];
     k1 = a.kv.kv_offsets[tid + 1];
   }
-  if (a.N > 0)  // as the gate call, which skips its last phase without candidates
-    gate_finish_body(a.N, a.nblocks, a.gws, a.selected, a.status,
-                     FinishLds{reinterpret_cast<uint32_t*>(smem), smem + kSortCap,
-                               smem + 2 * kSortCap});
+  const MaskLds lds(smem, a.R, a.budget);
+  int32_t* scratch = smem + mask_region(a.R, a.budget) / sizeof(int32_t);
+  if (kMode == kModeFlags) {
+    if (a.N > 0)  // as the gate call, which skips its last phase without candidates
+      gate_finish_body(a.N, a.nblocks, a.gws, a.selected, a.status,
+                       FinishLds{reinterpret_cast<uint32_t*>(smem), smem + kSortCap,
+                                 smem + 2 * kSortCap});
+    __syncthreads();
+    mask_body<kAligned>(tab, a.parent, a.token, a.selected, a.R, a.N, a.budget, a.q_offsets,
+                        a.slot_cand, a.slot_parent, a.slot_token, a.position_ids, a.tree_mask, a.W,
+                        first, a.status, smem);
+  } else {
+    SmallPool pool;
+    if (kMode == kModeSmall) pool = load_small(a);
+    const bool ok = mask_tables(tab, a.R, a.N, lds);
+    int bits = 0;
+    if (tid == 0 && !ok) bits |= ECHO_DATA_BAD_OFFSETS;
+    int count;
+    if (kMode == kModeSmall) {
+      count = select_small(a, pool, lds.offs, ok, first, scratch, lds.comp, s_cnt, &bits);
+    } else {
+      // (a malformed CSR leaves nothing selected)
+      count = select_from_lists(a, first, scratch, lds.comp, s_cnt);
+      if (count < 0) {  // uniform
+        gate_finish_body(a.N, a.nblocks, a.gws, a.selected, a.status,
+                         FinishLds{reinterpret_cast<uint32_t*>(scratch), scratch + kSortCap,
+                                   scratch + 2 * kSortCap});
+        __syncthreads();
+        uint32_t m0[kChunksPerLane];
+        load_round<kAligned>(a.selected, 0, a.N, m0);
+        count = mask_compact<kAligned>(a.selected, a.N, a.budget, m0, lds);
+      }
+    }
+    __syncthreads();
+    mask_slots(a.R, count, first, a.q_offsets, a.slot_cand, a.slot_parent, a.slot_token,
+               a.position_ids, lds);
+    if (first) {
+      __syncthreads();
+      bits |= mask_rows(a.parent, a.token, a.R, count, a.slot_cand, a.slot_parent, a.slot_token,
+                        a.position_ids, a.tree_mask, a.W, lds);
+      wave_status_or(a.status, bits);
+    }
+  }
+  if (first) return;
   __syncthreads();
-  mask_body<kAligned>(tab, a.parent, a.token, a.selected, a.R, a.N, a.budget, a.q_offsets,
-                      a.slot_cand, a.slot_parent, a.slot_token, a.position_ids, a.tree_mask, a.W,
-                      a.status, smem);
-  if (!a.plan) return;
-  __syncthreads();
-  // the slot offsets the mask phase just wrote are still in its LDS table
-  const int32_t* s_qoff = smem + (a.R + 1);
+  // the slot offsets just found are still in LDS
+  const int32_t* s_qoff = lds.qoff;
   RequestIn in;
   in.q0 = tid < a.R ? s_qoff[tid] : 0;
   in.q1 = tid < a.R ? s_qoff[tid + 1] : 0;
@@ -93,22 +303,48 @@ __global__ __launch_bounds__(kFrontThreads) void front_kernel(FrontArgs a) {
                                   a.aws, a.status, smem, pre ? &in : nullptr);
 }
 
+size_t plan_lds(int32_t R) {
+  return plan_table_words(R < kFrontThreads ? R : kFrontThreads) * sizeof(int32_t);
+}
+
+size_t mode_lds(int mode, int32_t N, int32_t R, int32_t budget) {
+  const size_t m = mask_lds_bytes(R, budget);
+  if (mode == kModeSmall) return mask_region(R, budget) + size_t(N) * 8;
+  if (mode == kModeLists) return mask_region(R, budget) + kFinishLds;
+  return m > kFinishLds ? m : kFinishLds;
+}
+
+template <bool kAligned, bool kWide>
+void (*front_of(int mode))(FrontArgs) {
+  if (mode == kModeSmall) return front_kernel<kAligned, kWide, kModeSmall>;
+  if (mode == kModeLists) return front_kernel<kAligned, kWide, kModeLists>;
+  return front_kernel<kAligned, kWide, kModeFlags>;
+}
+
+int front_mode(int32_t N, int32_t R, int32_t budget) {
+  constexpr size_t kMost = 150 * 1024;  // beside the phases' static LDS
+  if (N <= kSmallPool && mode_lds(kModeSmall, N, R, budget) <= kMost) return kModeSmall;
+  return mode_lds(kModeLists, N, R, budget) <= kMost ? kModeLists : kModeFlags;
+}
+
 }  // namespace
 
-size_t front_lds_bytes(int32_t R, int32_t budget) {
-  const size_t m = mask_lds_bytes(R, budget);
-  const size_t p = plan_table_words(R < kFrontThreads ? R : kFrontThreads) * sizeof(int32_t);
-  const size_t f = m > kFinishLds ? m : kFinishLds;
-  return f > p ? f : p;
+int front_gate_list(int32_t N, int32_t R, int32_t budget) {
+  const int mode = front_mode(N, R, budget);
+  return mode == kModeSmall ? -1 : mode == kModeLists ? 1 : 0;
 }
 
 int32_t launch_front(const FrontLaunch& f, hipStream_t stream) {
   (void)hipGetLastError();  // clear errors left by unrelated runtime calls
+  const int mode = front_mode(f.N, f.R, f.budget);
   FrontArgs a;
   a.N = f.N;
   a.nblocks = gate_blocks(f.N);
   a.gws = gate_ws_layout(f.gate_workspace, f.N, f.R);
   a.selected = f.selected;
+  a.logq = f.logq;
+  a.path_score = f.path_score;
+  a.num_selected = f.num_selected;
   a.cand_offsets = f.cand_offsets;
   a.parent = f.parent;
   a.token = f.token;
@@ -140,16 +376,17 @@ int32_t launch_front(const FrontLaunch& f, hipStream_t stream) {
   a.ucap = static_cast<long long>(unit_capacity(f.R, f.max_rows, f.hq, f.hkv));
   a.aws = attn_layout(f.attn_workspace, size_t(a.ucap), a.nb);
   a.status = f.status;
-  const size_t lds = front_lds_bytes(f.R, f.budget);
+  size_t lds = mode_lds(mode, f.N, f.R, f.budget);
+  if (lds < plan_lds(f.R)) lds = plan_lds(f.R);
   const bool aligned = (reinterpret_cast<uintptr_t>(f.selected) & 15u) == 0;
   const bool wide = attn_is_wide(f.R, f.max_rows, f.hq, f.hkv, a.kv.kv_rows, a.kv.kv_rows, a.nb);
-  auto kern = aligned ? (wide ? front_kernel<true, true> : front_kernel<true, false>)
-                      : (wide ? front_kernel<false, true> : front_kernel<false, false>);
+  const auto kern = aligned ? (wide ? front_of<true, true>(mode) : front_of<true, false>(mode))
+                            : (wide ? front_of<false, true>(mode) : front_of<false, false>(mode));
   if (lds > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
     return ECHO_ERR_HIP;
-  hipLaunchKernelGGL(kern, dim3(1), dim3(kFrontThreads), lds, stream, a);
+  hipLaunchKernelGGL(kern, dim3(a.plan ? 2 : 1), dim3(kFrontThreads), lds, stream, a);
   return hipGetLastError() == hipSuccess ? ECHO_OK : ECHO_ERR_HIP;
 }
 

@@ -127,44 +127,14 @@ __global__ __launch_bounds__(kGateThreads) void gate_score_kernel(
     if (ok) {
       const int r = upper_bound_idx(s_offs, R + 1, g);
       const int lo = s_offs[r];
-      const int n = g - lo;
       auto par_at = [&](int a) { return a >= wstart ? s_par[a - wstart] : parent[a]; };
       auto lq_at = [&](int a) { return a >= wstart ? s_lq[a - wstart] : logq[a]; };
-      int p = par_at(g);
-      if (p < -1 || p >= n) { bits |= ECHO_DATA_BAD_PARENT; p = -1; }
-      pg = p < 0 ? -1 : lo + p;
-      float own = lq_at(g);
-      if (own != own) { bits |= ECHO_DATA_NAN_LOGQ; own = -__builtin_inff(); }
-      else if (own > 0.0f) { bits |= ECHO_DATA_POS_LOGQ; own = 0.0f; }
-      // collect log q along the path, leaf first: vals[0] = own, vals[i] = i-th ancestor
-      float vals[ECHO_MAX_DEPTH + 1];
-      vals[0] = own;
-      int depth = 1;
-#pragma unroll
-      for (int i = 1; i <= ECHO_MAX_DEPTH; ++i) {
-        vals[i] = 0.0f;
-        if (p >= 0) {
-          const int a = lo + p;
-          float v = lq_at(a);
-          if (v != v) v = -__builtin_inff();
-          else if (v > 0.0f) v = 0.0f;
-          int pp = par_at(a);
-          if (pp < -1 || pp >= p) pp = -1;
-          vals[i] = v;
-          depth = i + 1;
-          p = pp;
-        }
-      }
-      if (depth > ECHO_MAX_DEPTH) {
-        bits |= ECHO_DATA_TOO_DEEP;
-      } else {
-        // root -> leaf: S = ((0 + lq[top]) + ...) + lq[own], one binary32 add per level
-        s = 0.0f;
-#pragma unroll
-        for (int i = ECHO_MAX_DEPTH; i >= 0; --i)
-          if (i < depth) s = s + vals[i];
-      }
-      key = score_key(s);
+      const NodeScore ns = node_score(g, lo, par_at, lq_at);
+      key = ns.key;
+      pg = ns.parent;
+      s = ns.score;
+      bits |= ns.bits;
+      const int depth = ns.depth;
       if (!sp.enabled) {
         if (key != 0u) atomicAdd(&s_hist[key >> kHistShift], 1u);
       } else if (key != 0u && ((sp.mask >> depth) & 1u)) {
@@ -368,36 +338,60 @@ __device__ BinResult find_bin(int nblocks, int budget, const GateWs& ws, bool re
 }
 
 // --------------------------------------------------------------- select ----
+// kList: the block's slice also receives the keys above b*, and all of it in index
+// order (for the fused step's front kernel, which compacts the selection from the
+// slices); else only the keys of b*, in any order.
+template <bool kList>
 __global__ __launch_bounds__(kGateThreads) void gate_select_kernel(int N, int nblocks, int budget,
                                                                    GateWs ws,
                                                                    uint8_t* __restrict__ selected,
                                                                    int32_t* __restrict__ num_selected,
                                                                    int32_t* status) {
   __shared__ uint32_t s_cnt;
+  __shared__ uint32_t s_wave[kGateThreads / kWave];
   const int g = blockIdx.x * kGateThreads + threadIdx.x;
   // this thread's key is fetched while the bin is found
   const uint32_t k = g < N ? ws.keys[g] : 0u;
-  if (threadIdx.x == 0) s_cnt = 0u;
+  if (!kList && threadIdx.x == 0) s_cnt = 0u;
   const BinResult br = find_bin(nblocks, budget, ws, blockIdx.x == 0, num_selected);
   const uint32_t m = br.m;
   const uint32_t bin = br.bin;
+  const uint32_t kb = k >> kHistShift;
+  const bool in = m != 0u && k != 0u && kb >= bin;  // (k == 0 past N)
   if (g < N) {
-    const uint32_t kb = k >> kHistShift;
-    if (m == 0u || k == 0u || kb < bin) {
+    if (!in) {
       selected[g] = 0;
     } else if (kb > bin) {
       // selected, and so is its parent: the child's score is the parent's plus a
       // clamped log q <= 0 in one binary32 add, so the parent's key (same walk,
       // same clamps) is never below the child's and lies in a higher bin too
       selected[g] = 1;
-    } else {
+    } else if (!kList) {
       const uint32_t slot = atomicAdd(&s_cnt, 1u);  // LDS; the order is fixed by the finish
       ws.cand[size_t(blockIdx.x) * kGateThreads + slot] = make_uint2(k, uint32_t(g));
     }
   }
   (void)status;  // nothing above the threshold bin can be unclosed (see above)
+  if (!kList) {
+    __syncthreads();
+    if (threadIdx.x == 0) ws.ccount[blockIdx.x] = s_cnt;
+    return;
+  }
+  const uint64_t bal = __ballot(in);
+  const int wid = int(threadIdx.x) / kWave;
+  if ((threadIdx.x & (kWave - 1)) == 0) s_wave[wid] = uint32_t(__popcll(bal));
   __syncthreads();
-  if (threadIdx.x == 0) ws.ccount[blockIdx.x] = s_cnt;
+  uint32_t before = 0u, total = 0u;
+#pragma unroll
+  for (int w = 0; w < kGateThreads / kWave; ++w) {
+    const uint32_t c = s_wave[w];
+    before += w < wid ? c : 0u;
+    total += c;
+  }
+  if (in)
+    ws.cand[size_t(blockIdx.x) * kGateThreads + before + uint32_t(lanes_below(bal))] =
+        make_uint2(k, uint32_t(g));
+  if (threadIdx.x == 0) ws.ccount[blockIdx.x] = total;
 }
 
 __global__ __launch_bounds__(kGateThreads) void gate_finish_kernel(int N, int nblocks, GateWs ws,
@@ -413,12 +407,14 @@ __global__ __launch_bounds__(kGateThreads) void gate_finish_kernel(int N, int nb
 
 namespace {
 
-// The gate's launches; the last phase (gate_finish) only if `finish`.
+// The gate's launches; the last phase (gate_finish) only if `finish`; `list`: see
+// gate_select.
 int32_t launch_gate_impl(const int32_t* cand_offsets, const int32_t* parent, const float* logq,
                          int32_t R, int32_t N, int32_t budget, const int32_t* sig_depth,
                          const float* log_tau, int32_t num_sig, float* path_score,
                          uint8_t* selected, int32_t* num_selected, int32_t* trunc_depth,
-                         void* workspace, int32_t* status, bool finish, hipStream_t stream) {
+                         void* workspace, int32_t* status, bool finish, bool list,
+                         hipStream_t stream) {
   (void)hipGetLastError();  // clear errors left by unrelated runtime calls
   GateWs ws = gate_ws_layout(workspace, N, R);
   const int blocks = gate_blocks(N);
@@ -444,8 +440,9 @@ int32_t launch_gate_impl(const int32_t* cand_offsets, const int32_t* parent, con
   if (sp.enabled)
     hipLaunchKernelGGL(gate_trunc_kernel, dim3(blocks), dim3(kGateThreads), lds, stream,
                        cand_offsets, R, N, ws, sp);
-  hipLaunchKernelGGL(gate_select_kernel, dim3(blocks), dim3(kGateThreads), 0, stream, N, blocks,
-                     budget, ws, selected, num_selected, status);
+  hipLaunchKernelGGL(list ? gate_select_kernel<true> : gate_select_kernel<false>, dim3(blocks),
+                     dim3(kGateThreads), 0, stream, N, blocks, budget, ws, selected, num_selected,
+                     status);
   if (N > 0 && finish) {
     hipLaunchKernelGGL(gate_finish_kernel, dim3(1), dim3(kGateThreads), 0, stream, N, blocks, ws,
                        selected, status);
@@ -462,16 +459,16 @@ int32_t launch_gate(const int32_t* cand_offsets, const int32_t* parent, const fl
                     hipStream_t stream) {
   return launch_gate_impl(cand_offsets, parent, logq, R, N, budget, sig_depth, log_tau, num_sig,
                           path_score, selected, num_selected, trunc_depth, workspace, status, true,
-                          stream);
+                          false, stream);
 }
 
 int32_t launch_gate_select_only(const int32_t* cand_offsets, const int32_t* parent,
                                 const float* logq, int32_t R, int32_t N, int32_t budget,
                                 float* path_score, uint8_t* selected, int32_t* num_selected,
-                                void* workspace, int32_t* status, hipStream_t stream) {
+                                void* workspace, int32_t* status, bool list, hipStream_t stream) {
   return launch_gate_impl(cand_offsets, parent, logq, R, N, budget, nullptr, nullptr, 0,
                           path_score, selected, num_selected, nullptr, workspace, status, false,
-                          stream);
+                          list, stream);
 }
 
 int32_t launch_gate_score(const int32_t* cand_offsets, const int32_t* parent, const float* logq,

@@ -78,6 +78,63 @@ __host__ __device__ inline GateWs gate_ws_layout(void* base, int32_t N, int32_t 
   return w;
 }
 
+// ---------------------------------------------------------------- score ----
+struct NodeScore {
+  float score;   // S after the clamps, -inf below ECHO_MAX_DEPTH
+  uint32_t key;  // its orderable key
+  int parent;    // clamped parent, global index (-1: child of the root)
+  int depth;     // 1 = child of the root; exact up to ECHO_MAX_DEPTH + 1
+  int bits;      // status bits
+};
+
+// Path score of candidate g, whose request's candidates start at lo: the root ->
+// leaf binary32 fold of eq. 5 with the clamps.  par_at(x) and lq_at(x) give the
+// parent (request-local) and log q of candidate x.
+template <typename ParAt, typename LqAt>
+__device__ __forceinline__ NodeScore node_score(int g, int lo, ParAt par_at, LqAt lq_at) {
+  NodeScore r;
+  r.bits = 0;
+  const int n = g - lo;
+  int p = par_at(g);
+  if (p < -1 || p >= n) { r.bits |= ECHO_DATA_BAD_PARENT; p = -1; }
+  r.parent = p < 0 ? -1 : lo + p;
+  float own = lq_at(g);
+  if (own != own) { r.bits |= ECHO_DATA_NAN_LOGQ; own = -__builtin_inff(); }
+  else if (own > 0.0f) { r.bits |= ECHO_DATA_POS_LOGQ; own = 0.0f; }
+  // collect log q along the path, leaf first: vals[0] = own, vals[i] = i-th ancestor
+  float vals[ECHO_MAX_DEPTH + 1];
+  vals[0] = own;
+  int depth = 1;
+#pragma unroll
+  for (int i = 1; i <= ECHO_MAX_DEPTH; ++i) {
+    vals[i] = 0.0f;
+    if (p >= 0) {
+      const int a = lo + p;
+      float v = lq_at(a);
+      if (v != v) v = -__builtin_inff();
+      else if (v > 0.0f) v = 0.0f;
+      int pp = par_at(a);
+      if (pp < -1 || pp >= p) pp = -1;
+      vals[i] = v;
+      depth = i + 1;
+      p = pp;
+    }
+  }
+  r.score = -__builtin_inff();
+  if (depth > ECHO_MAX_DEPTH) {
+    r.bits |= ECHO_DATA_TOO_DEEP;
+  } else {
+    // root -> leaf: S = ((0 + lq[top]) + ...) + lq[own], one binary32 add per level
+    r.score = 0.0f;
+#pragma unroll
+    for (int i = ECHO_MAX_DEPTH; i >= 0; --i)
+      if (i < depth) r.score = r.score + vals[i];
+  }
+  r.key = score_key(r.score);
+  r.depth = depth;
+  return r;
+}
+
 // --------------------------------------------------------------- finish ----
 // Radix selection: among the entries i < n with match(i), each carrying an
 // unsigned value val(i), find the value of the need-th largest, 8 bits at a
@@ -131,10 +188,28 @@ __device__ void radix_select(RadixSel& st, int n, Val val, Match match, RadixLds
     const int bits = st.shift >= 8 ? 8 : st.shift;
     const int nsh = st.shift - bits;
     const uint32_t pre = st.prefix, sh = uint32_t(st.shift);
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-      if (match(i)) {
-        const uint32_t v = val(i);
-        if ((v >> sh) == pre) atomicAdd(&L.h[cur][(v >> nsh) & ((1u << bits) - 1u)], 1u);
+    if (sh >= 32u) {
+      // no bit is known yet: all keys fall into a few bins (their leading bits are
+      // the sign and most of the exponent), so a wave adds once per distinct bin
+      for (int i0 = 0; i0 < n; i0 += blockDim.x) {
+        const int i = i0 + int(threadIdx.x);
+        const bool on = i < n && match(i);
+        const int d = on ? int(val(i) >> nsh) : 0;
+        uint64_t rem = __ballot(on);
+        while (rem != 0ull) {
+          const int lead = __builtin_ctzll(rem);
+          const int dl = __builtin_amdgcn_readlane(d, lead);
+          const uint64_t bal = __ballot(on && d == dl);
+          if (int(threadIdx.x & (kWave - 1)) == lead) atomicAdd(&L.h[cur][dl], uint32_t(__popcll(bal)));
+          rem &= ~bal;
+        }
+      }
+    } else {
+      for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        if (match(i)) {
+          const uint32_t v = val(i);
+          if ((v >> sh) == pre) atomicAdd(&L.h[cur][(v >> nsh) & ((1u << bits) - 1u)], 1u);
+        }
       }
     }
     __syncthreads();
@@ -156,19 +231,15 @@ __device__ void radix_select(RadixSel& st, int n, Val val, Match match, RadixLds
   __syncthreads();
 }
 
-// Threshold (thr_key, thr_g) of the selection: the bin_need-th largest of the
-// bin_cnt keys of bin b* under (key descending, index ascending).  keyv(i) and
-// idx(i) describe the n entries searched; every key of b* must be among them.
+// Threshold (thr_key, thr_g) of the selection: the st.need-th largest of the st.cnt
+// (> 0) keys with the known high bits st.prefix, under (key descending, index
+// ascending).  keyv(i) and idx(i) describe the n entries searched; every such key
+// must be among them.
 template <typename KeyV, typename Idx>
-__device__ void find_threshold(const GateMeta& mt, int n, int N, KeyV keyv, Idx idx, RadixLds& L,
+__device__ void find_threshold(RadixSel st, int n, int N, KeyV keyv, Idx idx, RadixLds& L,
                                uint32_t* thr_key, int32_t* thr_g) {
-  RadixSel st;
-  st.prefix = mt.bin;
-  st.shift = kHistShift;
-  st.need = mt.bin_need;
-  st.cnt = mt.bin_cnt;
   radix_select(st, n, keyv, [&](int i) { return keyv(i) != 0u; }, L);
-  const uint32_t K = st.prefix << st.shift;
+  const uint32_t K = st.shift >= 32 ? 0u : st.prefix << st.shift;  // 0: every key is selected
   int32_t tg = 0x7FFFFFFF;
   if (st.need < st.cnt) {
     // st.shift == 0: cnt keys equal K, the need-th smallest index among them
@@ -187,6 +258,14 @@ __device__ void find_threshold(const GateMeta& mt, int n, int N, KeyV keyv, Idx 
   *thr_g = tg;
 }
 
+// The same for the bin_need-th largest of the bin_cnt keys of bin b*.
+template <typename KeyV, typename Idx>
+__device__ void find_threshold(const GateMeta& mt, int n, int N, KeyV keyv, Idx idx, RadixLds& L,
+                               uint32_t* thr_key, int32_t* thr_g) {
+  find_threshold(RadixSel{mt.bin, kHistShift, mt.bin_need, mt.bin_cnt}, n, N, keyv, idx, L, thr_key,
+                 thr_g);
+}
+
 // LDS of the last phase that may come from a larger buffer: the gathered
 // candidates' keys and indices (kSortCap each) and the candidate offsets of
 // the select blocks (kGateThreads + 1).
@@ -195,6 +274,48 @@ struct FinishLds {
   int32_t* s_g;
   int* s_base;
 };
+
+// Ordered compaction of n <= kSortCap entries, entry i = k kGateThreads + tid on
+// thread tid: comp[0 ..) receives value(i) of those with sel(i), in the order of i,
+// at most cap of them.  Returns their number.  s_cnt: 8 x 16 words.  Contains one
+// barrier; s_cnt may be reused after another.
+template <typename Sel, typename Value>
+__device__ __forceinline__ int compact_entries(int n, Sel sel, Value value, int32_t* comp, int cap,
+                                               uint32_t* s_cnt) {
+  constexpr int kPer = kSortCap / kGateThreads, kW = kGateThreads / kWave;
+  static_assert(kPer * kW == 2 * kWave, "two counts per lane");
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+  uint32_t on = 0u;
+  int below[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = k * kGateThreads + int(threadIdx.x);
+    below[k] = 0;
+    uint32_t c = 0u;
+    if (k * kGateThreads < n) {  // uniform
+      const bool s = i < n && sel(i);
+      const uint64_t bal = __ballot(s);
+      c = uint32_t(__popcll(bal));
+      below[k] = lanes_below(bal);
+      on |= uint32_t(s) << k;
+    }
+    if (lane == 0) s_cnt[k * kW + wid] = c;
+  }
+  __syncthreads();
+  const uint32_t c0 = s_cnt[2 * lane], c1 = s_cnt[2 * lane + 1];
+  const uint32_t inc = wave_scan(c0 + c1, 0u, AddOp{});
+  const uint32_t excl = inc - c0 - c1;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    if (k * kGateThreads >= n) break;
+    const int e = k * kW + wid;
+    int pos = __builtin_amdgcn_readlane(int(excl), e >> 1) + below[k];
+    if (e & 1) pos += __builtin_amdgcn_readlane(int(c0), e >> 1);
+    if (((on >> k) & 1u) && pos < cap) comp[pos] = value(k * kGateThreads + int(threadIdx.x));
+  }
+  return __builtin_amdgcn_readlane(int(inc), kWave - 1);
+}
 
 // The last phase of the top-B selection, one workgroup of kGateThreads: gathers
 // the candidates of the threshold bin, finds the threshold (key descending,

@@ -33,13 +33,13 @@ __global__ __launch_bounds__(kMaskThreads) void mask_kernel(
   extern __shared__ int32_t smem[];
   const MaskTables tab = load_mask_tables(cand_offsets, root_token, prefix_len, R);
   mask_body<kAligned>(tab, parent, token, selected, R, N, budget, q_offsets, slot_cand,
-                      slot_parent, slot_token, position_ids, tree_mask, W, status, smem);
+                      slot_parent, slot_token, position_ids, tree_mask, W, true, status, smem);
 }
 
 }  // namespace
 
 size_t mask_lds_bytes(int32_t R, int32_t budget) {
-  return size_t(3 * (R + 1) + budget) * sizeof(int32_t) + size_t(budget) * sizeof(uint16_t);
+  return mask_words_bytes(R, budget);
 }
 
 int32_t launch_build_tree_mask(const int32_t* cand_offsets, const int32_t* parent,

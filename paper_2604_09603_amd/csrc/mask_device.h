@@ -115,58 +115,67 @@ __device__ __forceinline__ MaskTables load_mask_tables(const int32_t* __restrict
   return t;
 }
 
-// The whole flatten & pack on one workgroup of kMaskThreads, from the tables
-// load_mask_tables returned; `smem` holds mask_lds_bytes(R, budget) bytes of LDS.
-template <bool kAligned>
-__device__ void mask_body(
-    const MaskTables& tab, const int32_t* __restrict__ parent,
-    const int32_t* __restrict__ token, const uint8_t* __restrict__ selected, int R, int N,
-    int budget, int32_t* __restrict__ q_offsets, int32_t* __restrict__ slot_cand,
-    int32_t* __restrict__ slot_parent, int32_t* __restrict__ slot_token,
-    int32_t* __restrict__ position_ids, uint32_t* __restrict__ tree_mask, int W,
-    int32_t* status, int32_t* smem) {
-  int32_t* s_offs = smem;              // R + 1
-  int32_t* s_qoff = smem + (R + 1);    // R + 1
-  int32_t* s_plen = smem + 2 * (R + 1);  // R + 1 (prefix lengths)
-  int32_t* s_comp = smem + 3 * (R + 1);  // budget
-  // local slot of each packed node's nearest packed ancestor (0: the root)
-  uint16_t* s_pslot = reinterpret_cast<uint16_t*>(smem + 3 * (R + 1) + budget);
-  __shared__ int s_scan[kMaskThreads / kWave + 1];
-  __shared__ int s_flag;
+__host__ __device__ inline size_t mask_words_bytes(int32_t R, int32_t budget) {
+  return size_t(3 * (R + 1) + budget) * sizeof(int32_t) + size_t(budget) * sizeof(uint16_t);
+}
 
+// LDS of flatten & pack (mask_words_bytes(R, budget) bytes).
+struct MaskLds {
+  int32_t* offs;    // R + 1 candidate offsets
+  int32_t* qoff;    // R + 1 slot offsets
+  int32_t* plen;    // R + 1 prefix lengths
+  int32_t* comp;    // budget: the packed nodes, ascending
+  uint16_t* pslot;  // budget: local slot of each one's nearest packed ancestor (0: the root)
+  __device__ MaskLds(int32_t* smem, int R, int budget)
+      : offs(smem),
+        qoff(smem + (R + 1)),
+        plen(smem + 2 * (R + 1)),
+        comp(smem + 3 * (R + 1)),
+        pslot(reinterpret_cast<uint16_t*>(smem + 3 * (R + 1) + budget)) {}
+};
+
+// 0. The tables into LDS and the check of the CSR (starts at 0, ends at N, never
+// decreases): false if it is malformed.  A request's root token waits in its
+// slot-offset entry, which the same thread reads before it writes the offset in
+// step 2.
+__device__ __forceinline__ bool mask_tables(const MaskTables& tab, int R, int N,
+                                            const MaskLds& lds) {
+  __shared__ int s_flag;
   const int tid = threadIdx.x;
-  // the first round of flags is loaded together with the CSR
-  uint32_t m0[kChunksPerLane] = {};
-  if (N > 0) load_round<kAligned>(selected, 0, N, m0);
-  // the tables into LDS; a request's root token waits in its slot-offset entry,
-  // which the same thread reads before it writes the offset in step 2
 #pragma unroll
   for (int k = 0; k < kRootsPerThread; ++k) {
     const int r = tid + kMaskThreads * k;
-    if (r <= R) s_offs[r] = tab.offs[k];
+    if (r <= R) lds.offs[r] = tab.offs[k];
     if (r < R) {
-      s_plen[r] = tab.plen[k];
-      s_qoff[r] = tab.rtok[k];
+      lds.plen[r] = tab.plen[k];
+      lds.qoff[r] = tab.rtok[k];
     }
   }
   if (tid == 0) s_flag = 0;
   __syncthreads();
-  // the CSR: starts at 0, ends at N, never decreases (any failing thread sets the flag)
-  for (int r = tid; r <= R; r += kMaskThreads)
-    if ((r == 0 && s_offs[0] != 0) || (r == R && s_offs[R] != N) ||
-        (r < R && s_offs[r + 1] < s_offs[r]))
+  for (int r = tid; r <= R; r += kMaskThreads)  // any failing thread sets the flag
+    if ((r == 0 && lds.offs[0] != 0) || (r == R && lds.offs[R] != N) ||
+        (r < R && lds.offs[r + 1] < lds.offs[r]))
       s_flag = 1;
   __syncthreads();
-  const bool ok = s_flag == 0;
-  int bits = 0;
-  if (!ok && tid == 0) bits |= ECHO_DATA_BAD_OFFSETS;
+  return s_flag == 0;
+}
 
-  // 1. ordered compaction of the selection.  Within a wave the candidates run
-  // chunk by chunk (chunk v of every lane, lane order, then chunk v + 1), so a
-  // lane's position for chunk v is the wave's base, the wave's counts of the
-  // chunks before v, and the counts of chunk v in the lanes below it.
+// 1. Ordered compaction of the selection flags (m0: the first round of them) into
+// lds.comp, at most `budget` of them; returns how many are set.
+template <bool kAligned>
+__device__ __forceinline__ int mask_compact(const uint8_t* __restrict__ selected, int N, int budget,
+                                            const uint32_t (&m0)[kChunksPerLane],
+                                            const MaskLds& lds) {
+  __shared__ int s_scan[kMaskThreads / kWave + 1];
+  const int tid = threadIdx.x;
+  int32_t* s_comp = lds.comp;
+  // Within a wave the candidates run chunk by chunk (chunk v of every lane, lane
+  // order, then chunk v + 1), so a lane's position for chunk v is the wave's base,
+  // the wave's counts of the chunks before v, and the counts of chunk v in the
+  // lanes below it.
   int count = 0;  // uniform
-  if (ok) {
+  {
     const int lane = tid & (kWave - 1);
     for (int base = 0; base < N; base += kMaskThreads * kBytesPerThread) {
       uint32_t m[kChunksPerLane];
@@ -232,30 +241,55 @@ __device__ void mask_body(
       count += tot;
     }
   }
-  if (count > budget && tid == 0) bits |= ECHO_DATA_OVER_CAPACITY;
-  const int n_inc = count < budget ? count : budget;
-  __syncthreads();
+  return count;
+}
 
-  // 2. slot offsets and the root slots
+// 2. Slot offsets (LDS and q_offsets) and, if `roots`, the root slots, from the
+// n_inc packed nodes.
+__device__ __forceinline__ void mask_slots(int R, int n_inc, bool roots,
+                                           int32_t* __restrict__ q_offsets,
+                                           int32_t* __restrict__ slot_cand,
+                                           int32_t* __restrict__ slot_parent,
+                                           int32_t* __restrict__ slot_token,
+                                           int32_t* __restrict__ position_ids, const MaskLds& lds) {
+  const int tid = threadIdx.x;
 #pragma unroll
   for (int k = 0; k < kRootsPerThread; ++k) {
     const int r = tid + kMaskThreads * k;
     if (r >= R) break;
-    const int32_t root = s_qoff[r];
-    int v = r + lower_bound_lds(s_comp, 0, n_inc, s_offs[r]);
-    s_qoff[r] = v;
+    const int32_t root = lds.qoff[r];
+    const int v = r + lower_bound_lds(lds.comp, 0, n_inc, lds.offs[r]);
+    lds.qoff[r] = v;
     q_offsets[r] = v;
+    if (!roots) continue;
     slot_cand[v] = -1;
     slot_parent[v] = -1;
     slot_token[v] = root;
-    position_ids[v] = s_plen[r];
+    position_ids[v] = lds.plen[r];
   }
   if (tid == 0) {
-    s_qoff[R] = R + n_inc;
+    lds.qoff[R] = R + n_inc;
     q_offsets[R] = R + n_inc;
   }
-  __syncthreads();
+}
 
+// 3. and 4. The packed nodes' slots and every slot's ancestors (after a barrier).
+// Returns status bits.
+__device__ __forceinline__ int mask_rows(const int32_t* __restrict__ parent,
+                                         const int32_t* __restrict__ token, int R, int n_inc,
+                                         int32_t* __restrict__ slot_cand,
+                                         int32_t* __restrict__ slot_parent,
+                                         int32_t* __restrict__ slot_token,
+                                         int32_t* __restrict__ position_ids,
+                                         uint32_t* __restrict__ tree_mask, int W,
+                                         const MaskLds& lds) {
+  const int32_t* s_offs = lds.offs;
+  const int32_t* s_qoff = lds.qoff;
+  const int32_t* s_plen = lds.plen;
+  const int32_t* s_comp = lds.comp;
+  uint16_t* s_pslot = lds.pslot;
+  const int tid = threadIdx.x;
+  int bits = 0;
   // 3. nearest packed ancestor of every packed node, as a local slot
   for (int i = tid; i < n_inc; i += kMaskThreads) {
     const int g = s_comp[i];
@@ -324,6 +358,36 @@ __device__ void mask_body(
     for (int w = 0; w < kRegWords; ++w)
       if (w < W) row[w] = regs[w];
   }
+  return bits;
+}
+
+// The whole flatten & pack on one workgroup of kMaskThreads, from the tables
+// load_mask_tables returned; `smem` holds mask_lds_bytes(R, budget) bytes of LDS.
+// With `roots` false only the slot offsets are computed and written.
+template <bool kAligned>
+__device__ void mask_body(
+    const MaskTables& tab, const int32_t* __restrict__ parent,
+    const int32_t* __restrict__ token, const uint8_t* __restrict__ selected, int R, int N,
+    int budget, int32_t* __restrict__ q_offsets, int32_t* __restrict__ slot_cand,
+    int32_t* __restrict__ slot_parent, int32_t* __restrict__ slot_token,
+    int32_t* __restrict__ position_ids, uint32_t* __restrict__ tree_mask, int W, bool roots,
+    int32_t* status, int32_t* smem) {
+  const MaskLds lds(smem, R, budget);
+  // the first round of flags is loaded together with the CSR
+  uint32_t m0[kChunksPerLane] = {};
+  if (N > 0) load_round<kAligned>(selected, 0, N, m0);
+  const bool ok = mask_tables(tab, R, N, lds);
+  const int count = ok ? mask_compact<kAligned>(selected, N, budget, m0, lds) : 0;
+  const int n_inc = count < budget ? count : budget;
+  __syncthreads();
+  mask_slots(R, n_inc, roots, q_offsets, slot_cand, slot_parent, slot_token, position_ids, lds);
+  if (!roots) return;
+  int bits = 0;
+  if (threadIdx.x == 0 && !ok) bits |= ECHO_DATA_BAD_OFFSETS;
+  if (threadIdx.x == 0 && count > budget) bits |= ECHO_DATA_OVER_CAPACITY;
+  __syncthreads();
+  bits |= mask_rows(parent, token, R, n_inc, slot_cand, slot_parent, slot_token, position_ids,
+                    tree_mask, W, lds);
   wave_status_or(status, bits);
 }
 

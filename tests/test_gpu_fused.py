@@ -152,3 +152,27 @@ def test_fused_step_long_requests():
     _log("[fused] long requests")
     res = _compare(make_micro_batch(pool, 1200, hq=8, hkv=2, p_range=(0, 40), seed=9))
     assert int(np.diff(res["q_offsets"]).max()) > 256
+
+
+@pytest.mark.parametrize("n,budget,flat", [
+    (1, 4, False), (1024, 64, False), (3071, 300, False), (3072, 300, True), (3072, 16000, False),
+    (3073, 300, False), (8192, 300, True), (8193, 300, True), (30000, 12000, False)])
+def test_fused_step_front_modes(n, budget, flat):
+    """Every way in which the front kernel finds the selection, on both sides of
+    where it changes: a pool of up to 3072 candidates without gate launches, the
+    lists of the select launch up to the 8192 entries that LDS takes (flat: all
+    scores equal, so that every candidate is in the threshold bin), and the flags
+    beyond that."""
+    rng = np.random.default_rng(n + budget)
+    R = min(n, 37)
+    cuts = np.sort(rng.integers(0, n + 1, R - 1))
+    offs = np.concatenate([[0], cuts, [n]]).astype(np.int32)
+    local = np.concatenate([np.arange(k) for k in np.diff(offs)])
+    parent = np.where(rng.random(n) < 0.3, -1, (local - 1) // 2).astype(np.int32)
+    logq = np.zeros(n, np.float32) if flat else rng.choice(
+        np.array([0.0, -0.25, -0.5, -1.0, -3.0, -np.inf], np.float32), n)
+    pool = dict(cand_offsets=offs, parent=parent, token=rng.integers(0, 5, n).astype(np.int32),
+                logq=logq.astype(np.float32),
+                root_token=rng.integers(0, 5, R).astype(np.int32))
+    _log(f"[fused] front modes N={n} B={budget} flat={flat}")
+    _compare(make_micro_batch(pool, budget, hq=8, hkv=4, p_range=(0, 40), seed=n), repeat=2)
