@@ -3,11 +3,12 @@
 // the commit of each request's accepted path into a paged KV cache.
 //
 //   target_argmax   one workgroup per slot row: streams the row's bfloat16
-//                   logits with 16-byte loads, eight in flight per thread
-//                   (HBM-bound: Nq * V * 2 bytes), keeps per thread the first
-//                   largest value in its own index order; a workgroup reduction
-//                   picks the largest value, ties to the smaller token id.  Then
-//                   the acceptance kernel.
+//                   logits with 16-byte loads, two batches in flight per thread
+//                   (HBM-bound: Nq * V * 2 bytes), as ordered 16-bit integers: the
+//                   maximum of eight at a time, and the first block of eight that
+//                   holds the thread's largest; a workgroup reduction picks the
+//                   row's block and its first largest element.  Then the acceptance
+//                   kernel.
 //   commit_kv       one workgroup per request: copies the root slot's and the
 //                   accepted slots' K and V rows into their pages, then advances
 //                   the request's cached length.
@@ -17,116 +18,153 @@
 namespace echo {
 namespace {
 
-constexpr int kArgThreads = 512;  // two workgroups per CU: every slot row of a batch is resident
-constexpr int kArgUnroll = 8;  // 16-byte loads in flight per thread
 constexpr int kCommitThreads = 256;
-constexpr uint32_t kNoIdx = 0xFFFFFFFFu;
+typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
+typedef short short2v __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+// Two bfloat16 as signed 16-bit integers in their numeric order (-0 below +0;
+// negative NaN below -inf, positive NaN above +inf).
+__device__ __forceinline__ short2v ordered(uint32_t w) {
+  const short2v x = __builtin_bit_cast(short2v, w);
+  return x ^ ((x >> short2v{15, 15}) & short2v{0x7FFF, 0x7FFF});
+}
+constexpr int kOrdInf = 0x7F80;        // +inf
+constexpr int kOrdNegInf = -0x7F80 - 1;  // -inf
 
-// One workgroup per slot row.  Each thread keeps the first strictly largest
-// value of its own elements, visited in increasing index order (a NaN never
-// compares greater, so it is never kept; -0 and +0 compare equal); the
-// workgroup then takes the largest value, ties to the smaller index.  A row
-// in which nothing beats -inf (only -inf and NaN) is resolved by a second
-// scan for its first -inf (a row of NaN only gives 0).
-__global__ __launch_bounds__(kArgThreads) void target_argmax_kernel(
+// The row's argmax element by element, for the rows whose order as integers is not
+// the order asked for: NaN (never wins over a number), a maximum of zero (-0 and +0
+// are equal) or nothing above -inf (then the first -inf; only NaN: 0).  Every thread
+// of the workgroup calls it; the result is in s_best (value above, ~index below).
+template <int NT>
+__device__ __forceinline__ uint32_t argmax_plain(const uint16_t* row, long long vocab,
+                                                 unsigned long long* s_best) {
+  __syncthreads();
+  if (threadIdx.x == 0) *s_best = 0ull;
+  __syncthreads();
+  unsigned long long best = 0ull;
+  for (long long v = threadIdx.x; v < vocab; v += NT) {
+    const uint32_t u = uint32_t(row[v]);
+    if ((u & 0x7FFFu) > 0x7F80u) continue;  // NaN
+    const uint32_t b = u == 0x8000u ? 0u : u;  // -0 -> +0
+    const uint32_t k = (b & 0x8000u) ? (~b & 0xFFFFu) : (b | 0x8000u);
+    const unsigned long long w =
+        ((unsigned long long)(k + 1u) << 32) | (0xFFFFFFFFu - uint32_t(v));
+    best = w > best ? w : best;
+  }
+  if (best != 0ull) atomicMax(s_best, best);
+  __syncthreads();
+  return *s_best == 0ull ? 0u : 0xFFFFFFFFu - uint32_t(*s_best);
+}
+
+// One workgroup of NT threads per slot row, kArgBatch 16-byte loads per batch.
+// * At most one row per CU: 1024 threads keep the most bytes in flight.  160 rows of
+//   128,256 (41 MB): 11.9 -> 10.4 us.
+// * More rows: 512 threads, two or more workgroups of which share a CU, longer
+//   batches, and loads with the non-temporal hint, as the logits no longer stay in
+//   the caches.  384 rows of 151,936 (117 MB): 26.4 -> 22.0 us, 5.3 TB/s (24.0
+//   without the hint, 25.5 with batches of 12; the 128 CUs with two rows set the
+//   end).  For the smaller case the hint is slower (12.0).
+// (Before: one batch of eight loads at a time, compared as floats element by
+// element, four instructions each, and a remainder of single loads.)
+template <int NT, int kArgBatch, bool kStream>
+__global__ __launch_bounds__(NT) void target_argmax_kernel(
     const uint16_t* __restrict__ logits, long long vocab, const int32_t* __restrict__ q_offsets,
     int R, int32_t* __restrict__ target) {
-  __shared__ float s_val[kArgThreads / kWave];
-  __shared__ uint32_t s_idx[kArgThreads / kWave];
-  __shared__ uint32_t s_first_inf;
+  __shared__ unsigned long long s_wave[NT / kWave];
+  __shared__ unsigned long long s_best;
   const int s = blockIdx.x;
-  const int nq = q_offsets[R];
-  if (s >= nq) return;  // uniform over the workgroup
   const uint16_t* row = logits + size_t(s) * size_t(vocab);
   const int tid = threadIdx.x;
-  float best = -__builtin_inff();
-  uint32_t bidx = kNoIdx;
-  auto take = [&](float v, uint32_t i) {
-    if (v > best) {
-      best = v;
-      bidx = i;
-    }
-  };
-  // scalar head up to 16-byte alignment, 8-value body, scalar tail
+  // scalar head up to 16-byte alignment, blocks of 8, scalar tail
   const long long head =
       min<long long>(vocab, ((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) / 2);
   const long long nvec = (vocab - head) / 8;
   const long long tail0 = head + nvec * 8;
-  // the head precedes the body in index order: its elements are taken first
-  for (long long v = tid; v < head; v += kArgThreads)
-    take(__uint_as_float(uint32_t(row[v]) << 16), uint32_t(v));
   const uint4* body = reinterpret_cast<const uint4*>(row + head);
-  long long c = tid;
-  for (; c + (kArgUnroll - 1) * kArgThreads < nvec; c += kArgUnroll * kArgThreads) {
-    uint4 x[kArgUnroll];
-#pragma unroll
-    for (int u = 0; u < kArgUnroll; ++u) x[u] = body[c + u * kArgThreads];
-#pragma unroll
-    for (int u = 0; u < kArgUnroll; ++u) {
-      const uint32_t v0 = uint32_t(head + (c + u * kArgThreads) * 8);
-      take(bf16_lo(x[u].x), v0 + 0);
-      take(bf16_hi(x[u].x), v0 + 1);
-      take(bf16_lo(x[u].y), v0 + 2);
-      take(bf16_hi(x[u].y), v0 + 3);
-      take(bf16_lo(x[u].z), v0 + 4);
-      take(bf16_hi(x[u].z), v0 + 5);
-      take(bf16_lo(x[u].w), v0 + 6);
-      take(bf16_hi(x[u].w), v0 + 7);
+  if (s >= q_offsets[R]) return;  // uniform over the workgroup
+  int best = -0x8000 - 1;  // below every ordered value
+  uint32_t at = 0u;        // its element (head, tail) or the first one of its block
+  // the head precedes the blocks in index order: taken first
+  for (long long v = tid; v < head; v += NT) {
+    const int o = int(ordered(row[v])[0]);
+    if (o > best) {
+      best = o;
+      at = uint32_t(v);
     }
   }
-  for (; c < nvec; c += kArgThreads) {
-    const uint4 x = body[c];
-    const uint32_t v0 = uint32_t(head + c * 8);
-    take(bf16_lo(x.x), v0 + 0);
-    take(bf16_hi(x.x), v0 + 1);
-    take(bf16_lo(x.y), v0 + 2);
-    take(bf16_hi(x.y), v0 + 3);
-    take(bf16_lo(x.z), v0 + 4);
-    take(bf16_hi(x.z), v0 + 5);
-    take(bf16_lo(x.w), v0 + 6);
-    take(bf16_hi(x.w), v0 + 7);
+  if (nvec > 0) {
+    // blocks past the last one repeat it (no effect: same value, same place)
+    const auto load = [&](uint4 (&x)[kArgBatch], long long c) {
+#pragma unroll
+      for (int u = 0; u < kArgBatch; ++u) {
+        const long long i = c + (long long)u * NT;
+        const uint4* p = body + (i < nvec ? i : nvec - 1);
+        if (kStream) {
+          const uint32x4 q = __builtin_nontemporal_load(reinterpret_cast<const uint32x4*>(p));
+          x[u] = make_uint4(q[0], q[1], q[2], q[3]);
+        } else {
+          x[u] = *p;
+        }
+      }
+    };
+    const auto take = [&](const uint4 (&x)[kArgBatch], long long c) {
+#pragma unroll
+      for (int u = 0; u < kArgBatch; ++u) {
+        const long long i = c + (long long)u * NT;
+        const short2v m = __builtin_elementwise_max(
+            __builtin_elementwise_max(ordered(x[u].x), ordered(x[u].y)),
+            __builtin_elementwise_max(ordered(x[u].z), ordered(x[u].w)));
+        const int o = max(int(m[0]), int(m[1]));
+        if (o > best) {
+          best = o;
+          at = uint32_t(head + (i < nvec ? i : nvec - 1) * 8);
+        }
+      }
+    };
+    constexpr long long kStep = (long long)kArgBatch * NT;
+    uint4 x0[kArgBatch], x1[kArgBatch];
+    load(x0, tid);
+    for (long long c = tid; c - tid < nvec; c += 2 * kStep) {
+      load(x1, c + kStep);
+      take(x0, c);
+      load(x0, c + 2 * kStep);
+      take(x1, c + kStep);
+    }
   }
-  // the tail follows every body element in index order
-  for (long long v = tail0 + tid; v < vocab; v += kArgThreads)
-    take(__uint_as_float(uint32_t(row[v]) << 16), uint32_t(v));
-  // workgroup: largest value, ties (and -0 == +0) to the smaller index
-  auto better = [](float va, uint32_t ia, float vb, uint32_t ib) {
-    if (ib == kNoIdx) return false;
-    if (ia == kNoIdx) return true;
-    return vb > va || (vb == va && ib < ia);
-  };
+  for (long long v = tail0 + tid; v < vocab; v += NT) {
+    const int o = int(ordered(row[v])[0]);
+    if (o > best) {
+      best = o;
+      at = uint32_t(v);
+    }
+  }
+  // largest value, then the smallest place
+  unsigned long long w =
+      ((unsigned long long)(uint32_t(best + 0x8001)) << 32) | (0xFFFFFFFFu - at);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
-    const float ov = __shfl_xor(best, off, kWave);
-    const uint32_t oi = uint32_t(__shfl_xor(int(bidx), off, kWave));
-    if (better(best, bidx, ov, oi)) {
-      best = ov;
-      bidx = oi;
-    }
+    const unsigned long long o = __shfl_xor(w, off, kWave);
+    w = o > w ? o : w;
   }
-  if ((tid & (kWave - 1)) == 0) {
-    s_val[tid / kWave] = best;
-    s_idx[tid / kWave] = bidx;
-  }
-  if (tid == 0) s_first_inf = kNoIdx;
+  if ((tid & (kWave - 1)) == 0) s_wave[tid / kWave] = w;
   __syncthreads();
-  float bv = s_val[0];
-  uint32_t bi = s_idx[0];
-  for (int w = 1; w < kArgThreads / kWave; ++w)
-    if (better(bv, bi, s_val[w], s_idx[w])) {
-      bv = s_val[w];
-      bi = s_idx[w];
-    }
-  if (bi == kNoIdx) {  // nothing above -inf: the first -inf, else 0
-    for (long long v = tid; v < vocab; v += kArgThreads)
-      if (row[v] == 0xFF80u) atomicMin(&s_first_inf, uint32_t(v));
-    __syncthreads();
-    bi = s_first_inf == kNoIdx ? 0u : s_first_inf;
+#pragma unroll
+  for (int k = 0; k < NT / kWave; ++k) w = s_wave[k] > w ? s_wave[k] : w;
+  const int top = int(uint32_t(w >> 32)) - 0x8001;
+  uint32_t idx = 0xFFFFFFFFu - uint32_t(w);
+  if (top > kOrdInf || top == 0 || top <= kOrdNegInf) {  // uniform, rare
+    idx = argmax_plain<NT>(row, vocab, &s_best);
+  } else if (idx >= head && (long long)idx < tail0) {
+    // the first of the block's eight elements with that value
+    const uint4 x = *reinterpret_cast<const uint4*>(row + idx);
+    const short2v o[4] = {ordered(x.x), ordered(x.y), ordered(x.z), ordered(x.w)};
+    uint32_t e = 7u;
+#pragma unroll
+    for (int k = 6; k >= 0; --k)
+      if (int(o[k >> 1][k & 1]) == top) e = uint32_t(k);
+    idx += e;
   }
-  if (tid == 0) target[s] = int32_t(bi);
+  if (tid == 0) target[s] = int32_t(idx);
 }
 
 __global__ __launch_bounds__(kCommitThreads) void commit_kv_kernel(
@@ -188,9 +226,12 @@ int32_t launch_accept_logits(const int32_t* q_offsets, const int32_t* slot_paren
                              int32_t* accept_len, int32_t* accept_slots, int32_t* bonus_token,
                              int32_t* status, hipStream_t stream) {
   (void)hipGetLastError();
-  if (max_rows > 0)
-    hipLaunchKernelGGL(target_argmax_kernel, dim3(max_rows), dim3(kArgThreads), 0, stream,
-                       logits, static_cast<long long>(vocab), q_offsets, R, target);
+  if (max_rows > 0) {
+    const bool few = max_rows <= device_cu_count();
+    auto kern = few ? target_argmax_kernel<1024, 5, false> : target_argmax_kernel<512, 10, true>;
+    hipLaunchKernelGGL(kern, dim3(max_rows), dim3(few ? 1024 : 512), 0, stream, logits,
+                       static_cast<long long>(vocab), q_offsets, R, target);
+  }
   if (hipGetLastError() != hipSuccess) return ECHO_ERR_HIP;
   return launch_accept(q_offsets, slot_parent, slot_token, target, R, max_rows, max_depth,
                        accept_len, accept_slots, bonus_token, status, stream);

@@ -173,6 +173,38 @@ def test_accept_from_logits(name, vocab, ties):
                         nan_rows=2 if name == "tiny" else 0)
 
 
+@pytest.mark.parametrize("vocab", [1, 7, 8, 9, 40959, 81920 + 8, 49153])
+@pytest.mark.parametrize("rows", [5, 300])
+def test_target_argmax_edges(vocab, rows):
+    """Row lengths on both sides of the 16-byte blocks (odd ones misalign the rows)
+    and of the batches of 10 x 512 and 5 x 1024 blocks, few rows and more than the
+    GPU has CUs; in the first rows what integer order does not decide: NaN of both
+    signs, a largest value of zero with both signs, only -inf, -inf and NaN, only
+    NaN.  Against the oracle, exactly."""
+    import torch
+    import paper_2604_09603_amd as pkg
+    rng = np.random.default_rng(vocab + rows)
+    vals = rng.integers(-40, 3, (rows, vocab)).astype(np.float32) / 4
+    bits = synth.f32_to_bf16_bits(vals).reshape(rows, vocab).copy()
+    neg = (bits >> 15) & 1
+    bits[0] = np.where(rng.random(vocab) < 0.3, 0x7FC0 | (neg[0] << 15), bits[0])
+    bits[1] = np.where(vals[1] >= 0, np.where(rng.random(vocab) < 0.5, 0x8000, 0), bits[1])
+    bits[2] = 0xFF80
+    bits[3] = np.where(rng.random(vocab) < 0.5, 0xFF80, 0x7F81)
+    bits[4] = np.where(rng.random(vocab) < 0.5, 0xFFC1, 0x7FC0)
+    i32 = lambda *s: torch.zeros(s, dtype=torch.int32, device="cuda:0")
+    target = i32(rows)
+    qo = np.arange(rows + 1, dtype=np.int32)
+    _log(f"[serve] argmax V={vocab} rows={rows}")
+    pkg.echo_accept_logits(_dev(qo), _dev(np.full(rows, -1, np.int32)), i32(rows),
+                           _dev(bits.view(np.int16)), rows, rows, 16, target, i32(rows),
+                           i32(rows, 16), i32(rows))
+    torch.cuda.synchronize()
+    want = oracle.accept_from_logits(qo, np.full(rows, -1, np.int32), np.zeros(rows, np.int32),
+                                     bits, 16)
+    assert np.array_equal(target.cpu().numpy(), want["target_token"])
+
+
 def test_commit_kv_matches_oracle():
     import torch
     import paper_2604_09603_amd as pkg
