@@ -22,17 +22,14 @@ int32_t launch_gate_select_only(const int32_t* cand_offsets, const int32_t* pare
                                 float* path_score, uint8_t* selected, int32_t* num_selected,
                                 void* workspace, int32_t* status, bool list, hipStream_t stream);
 
-// Path scores only (the first gate launch): per candidate the orderable key
-// (0 = never selectable), the clamped parent as a global index (-1: child of
-// the root) and the depth (capped at ECHO_MAX_DEPTH + 1), in the gate workspace.
+// Path scores of the elastic scheduler, in the gate workspace: per candidate the
+// orderable key (0 = never selectable), the clamped parent as a global index (-1:
+// child of the root) and the depth (capped at ECHO_MAX_DEPTH + 1).
 struct GateScoreBufs {
   const uint32_t* keys;
   const int32_t* pglob;
   const uint8_t* depth;
 };
-int32_t launch_gate_score(const int32_t* cand_offsets, const int32_t* parent, const float* logq,
-                          int32_t R, int32_t N, float* path_score, void* workspace,
-                          int32_t* status, hipStream_t stream, GateScoreBufs* out);
 
 // Alg. 1 scheduler (checkpoint table as for launch_gate; w_topk >= 1, w_max >= 0).
 int32_t launch_gate_elastic(const int32_t* cand_offsets, const int32_t* parent, const float* logq,

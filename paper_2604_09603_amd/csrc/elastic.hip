@@ -6,26 +6,32 @@
 // or fails and is truncated.  Phase 2 widens every truncated request's last
 // kept depth up to W_max nodes while budget is left.
 //
-// Four launches.  The coupling between requests is only through the budget,
-// and until the budget runs out every request receives its whole demand, so
-// each request's phase-1 trajectory can be computed on its own:
+// Two launches (three beyond kFinThreads requests).  The coupling between requests
+// is only through the budget, and until the budget runs out every request receives
+// its whole demand, so each request's phase-1 trajectory can be computed on its own:
 //
-//   gate_score        (shared with the top-B gate) keys, clamped parents, depths
-//   elastic_request   one workgroup per request: its full-grant trajectory --
-//                     per depth the appendable candidates (parent held), the
-//                     checkpoint test, the demand min(W_topk, #appendable) and
-//                     every appendable candidate's rank (key descending, index
-//                     ascending); the first failed checkpoint and the phase-2
-//                     demand at the depth above it
-//   elastic_finish    one workgroup: walks the depths with the budget, finds the
-//                     depth where the demands reach what is left and grants it
-//                     in request order; otherwise grants the phase-2 demands in
-//                     request order
-//   elastic_select    one thread per candidate: selected iff its rank is below
-//                     its request's grant at its depth (or inside the phase-2
-//                     grant at the widened depth); checks ancestor closure
+//   elastic_request   one workgroup per request: its candidates' path scores, then
+//                     its full-grant trajectory -- per depth the appendable
+//                     candidates (parent held), the checkpoint test, the demand
+//                     min(W_topk, #appendable) and every appendable candidate's
+//                     rank (key descending, index ascending); the first failed
+//                     checkpoint and the phase-2 demand at the depth above it
+//   elastic_select    every workgroup first walks the depths with the budget, finds
+//                     the depth where the demands reach what is left and grants it
+//                     in request order, or else grants the phase-2 demands in
+//                     request order (more requests than it has threads: a launch
+//                     of one workgroup, elastic_finish, does this).  Then one thread
+//                     per candidate: selected iff its rank is below its request's
+//                     grant at its depth (or inside the phase-2 grant at the widened
+//                     depth); checks ancestor closure
+//
+// Latency-bound, chains of round trips and barriers.  At 128 requests and 90,880
+// candidates the two launches take 20.5 and 7.0 us; as four, with the scores and the
+// grants in launches of their own, they took 6.8, 16.1, 4.1 and 4.4, and a launch
+// boundary more each.
 #include "echo_device.h"
 #include "echo_internal.h"
+#include "gate_device.h"
 
 namespace echo {
 namespace {
@@ -201,10 +207,105 @@ __device__ __forceinline__ bool level_test(int d, int A, uint32_t mx, const Elas
   return A > 0;  // none appendable: the drafted tree is exhausted
 }
 
-// Trajectory of a request whose candidates fit in LDS: they are grouped by
-// depth once, so each depth visits only its own candidates.
-__device__ void trajectory_staged(int r, int lo, int n, const GateScoreBufs& sb,
-                                  const ElasticArgs& ea, const ElasticWs& ew, ElasticLds& L) {
+// What the request workgroups read of the pool and write for the select launch.
+struct ElasticPool {
+  const int32_t* parent;
+  const float* logq;
+  float* path_score;  // nullable
+  uint32_t* keys;     // orderable key, 0 = never selectable
+  int32_t* pglob;     // clamped parent, global index (-1: child of the root)
+  uint8_t* depth;     // capped at ECHO_MAX_DEPTH + 1
+};
+
+// Path scores of a request whose candidates fit in LDS, top-down, all candidates of a
+// depth in one round (each folds the same binary32 adds in the same order as a walk
+// from the root): L.key, L.par, L.dep and the pool's outputs.  Returns status bits.
+__device__ int staged_scores(int lo, int n, const ElasticPool& ep, ElasticLds& L) {
+  constexpr uint32_t kUnknown = 0x7FFFFFFFu;  // a NaN: no clamped score is one
+  // kPer candidates per thread in registers: a round is one LDS round trip (read
+  // from LDS one after another, three each, the rounds took 4 us).  Requests with
+  // more take several passes; a candidate's parent is never in a later one.
+  constexpr int kPer = 4;
+  const int tid = threadIdx.x;
+  int bits = 0;
+  for (int i0 = 0; i0 < n; i0 += kPer * kElThreads) {  // uniform
+    int pp[kPer];
+    float lq[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = i0 + tid + q * kElThreads;
+      pp[q] = i < n ? ep.parent[lo + i] : -1;
+      lq[q] = i < n ? ep.logq[lo + i] : 0.0f;
+    }
+    uint32_t open = 0u;  // bit q: candidate q has no score yet
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = i0 + tid + q * kElThreads;
+      if (i >= n) continue;
+      if (pp[q] < -1 || pp[q] >= i) { bits |= ECHO_DATA_BAD_PARENT; pp[q] = -1; }
+      if (lq[q] != lq[q]) { bits |= ECHO_DATA_NAN_LOGQ; lq[q] = -__builtin_inff(); }
+      else if (lq[q] > 0.0f) { bits |= ECHO_DATA_POS_LOGQ; lq[q] = 0.0f; }
+      const bool top = pp[q] < 0;
+      L.par[i] = pp[q];
+      L.word[i] = top ? (uint64_t(1) << 32) | __float_as_uint(0.0f + lq[q]) : kUnknown;
+      open |= uint32_t(!top) << q;
+    }
+    // after ECHO_MAX_DEPTH - 1 rounds every node of depth <= ECHO_MAX_DEPTH is known
+    for (int round = 1; round < ECHO_MAX_DEPTH; ++round) {
+      if (!__syncthreads_or(open != 0u)) break;
+      uint64_t v[kPer];
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) v[q] = ((open >> q) & 1u) ? L.word[pp[q]] : kUnknown;
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        if (uint32_t(v[q]) == kUnknown || uint32_t(v[q] >> 32) >= ECHO_MAX_DEPTH) continue;
+        const float s = __uint_as_float(uint32_t(v[q])) + lq[q];
+        L.word[i0 + tid + q * kElThreads] = (((v[q] >> 32) + 1) << 32) | __float_as_uint(s);
+        open &= ~(1u << q);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = i0 + tid + q * kElThreads;
+      if (i >= n) continue;
+      const bool known = !((open >> q) & 1u);
+      if (!known) bits |= ECHO_DATA_TOO_DEEP;
+      const uint64_t v = L.word[i];
+      const float s = known ? __uint_as_float(uint32_t(v)) : -__builtin_inff();
+      const int d = known ? int(v >> 32) : ECHO_MAX_DEPTH + 1;
+      const uint32_t k = score_key(s);
+      L.key[i] = k;
+      L.dep[i] = uint8_t(d);
+      ep.keys[lo + i] = k;
+      ep.pglob[lo + i] = pp[q] < 0 ? -1 : lo + pp[q];
+      ep.depth[lo + i] = uint8_t(d);
+      if (ep.path_score != nullptr) ep.path_score[lo + i] = s;
+    }
+  }
+  return bits;
+}
+
+// The same for a request too large for LDS: each candidate walks its path in memory.
+__device__ int global_scores(int lo, int n, const ElasticPool& ep) {
+  int bits = 0;
+  for (int g = lo + int(threadIdx.x); g < lo + n; g += kElThreads) {
+    const NodeScore ns = node_score(g, lo, [&](int x) { return ep.parent[x]; },
+                                    [&](int x) { return ep.logq[x]; });
+    bits |= ns.bits;
+    ep.keys[g] = ns.key;
+    ep.pglob[g] = ns.parent;
+    ep.depth[g] = uint8_t(min(ns.depth, ECHO_MAX_DEPTH + 1));
+    if (ep.path_score != nullptr) ep.path_score[g] = ns.score;
+  }
+  return bits;
+}
+
+// Trajectory of a request whose candidates fit in LDS (staged_scores left them
+// there): they are grouped by depth once, so each depth visits only its own
+// candidates.
+__device__ void trajectory_staged(int r, int lo, int n, const ElasticArgs& ea, const ElasticWs& ew,
+                                  ElasticLds& L) {
   const int tid = threadIdx.x;
   if (tid <= kSlots) L.off[tid] = 0;
   if (tid < kSlots) {
@@ -217,29 +318,14 @@ __device__ void trajectory_staged(int r, int lo, int n, const GateScoreBufs& sb,
     L.mx[tid] = 0u;
   }
   __syncthreads();
-  // all of this thread's candidates are fetched before any is stored, so the
-  // loads overlap instead of paying the memory latency once per candidate
-  constexpr int kPer = kElCap / kElThreads;
-  uint32_t kk[kPer];
-  int pp[kPer], dd[kPer];
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int i = tid + q * kElThreads;
-    kk[q] = i < n ? sb.keys[lo + i] : 0u;
-    pp[q] = i < n ? sb.pglob[lo + i] : -1;
-    dd[q] = i < n ? int(sb.depth[lo + i]) : 0;
-  }
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int i = tid + q * kElThreads;
+  for (int i0 = 0; i0 < n; i0 += kElThreads) {  // bounds uniform in the workgroup
+    const int i = i0 + tid;
     if (i < n) {
-      L.key[i] = kk[q];
-      L.par[i] = pp[q] < 0 ? -1 : pp[q] - lo;
-      L.dep[i] = uint8_t(dd[q]);
       L.sel[i] = 0;
       ew.rank[lo + i] = -1;
     }
-    add_by_depth(i < n && kk[q] != 0u, dd[q] + 1, L.off);  // finite keys have depth <= 16
+    const bool on = i < n && L.key[i] != 0u;  // finite keys have depth <= 16
+    add_by_depth(on, on ? int(L.dep[i]) + 1 : 0, L.off);
   }
   __syncthreads();
   if (tid < kWave) {  // inclusive scan of the depth counts (18 entries) in one wave
@@ -340,17 +426,41 @@ __device__ void trajectory_global(int r, int lo, int n, const GateScoreBufs& sb,
 }
 
 __global__ __launch_bounds__(kElThreads) void elastic_request_kernel(
-    const int32_t* __restrict__ cand_offsets, int N, GateScoreBufs sb, ElasticArgs ea,
-    ElasticWs ew) {
+    const int32_t* __restrict__ cand_offsets, int R, int N, ElasticPool ep, ElasticArgs ea,
+    ElasticWs ew, int32_t* status) {
   __shared__ ElasticLds L;
   const int r = blockIdx.x;
   int lo = cand_offsets[r], hi = cand_offsets[r + 1];
-  // a malformed CSR leaves every key at 0 (nothing appendable); only keep the
-  // range in bounds
-  if (lo < 0 || hi > N || hi < lo) lo = hi = 0;
+  // the candidate CSR must be well formed before anything is read through it; a
+  // malformed one leaves every key at 0 (nothing appendable)
+  bool bad = false;
+  for (int i = threadIdx.x; i <= R; i += kElThreads) {
+    const int o = cand_offsets[i];
+    bad = bad || (i == 0 && o != 0) || (i == R && o != N) || (i < R && cand_offsets[i + 1] < o);
+  }
+  int bits = 0;
+  if (__syncthreads_or(bad)) {
+    lo = int((long long)N * r / R);
+    hi = int((long long)N * (r + 1) / R);
+    for (int g = lo + int(threadIdx.x); g < hi; g += kElThreads) {
+      ep.keys[g] = 0u;
+      ep.pglob[g] = -1;
+      if (ep.path_score != nullptr) ep.path_score[g] = -__builtin_inff();
+    }
+    if (r == 0 && threadIdx.x == 0) bits |= ECHO_DATA_BAD_OFFSETS;
+    lo = hi = 0;
+  }
   const int n = hi - lo;
-  if (n <= kElCap) trajectory_staged(r, lo, n, sb, ea, ew, L);
-  else trajectory_global(r, lo, n, sb, ea, ew, L);
+  if (n <= kElCap) {
+    bits |= staged_scores(lo, n, ep, L);
+    __syncthreads();
+    trajectory_staged(r, lo, n, ea, ew, L);
+  } else {
+    bits |= global_scores(lo, n, ep);
+    __syncthreads();
+    trajectory_global(r, lo, n, GateScoreBufs{ep.keys, ep.pglob, ep.depth}, ea, ew, L);
+  }
+  wave_status_or(status, bits);
 }
 
 // -------------------------------------------------------------- finish ----
@@ -464,14 +574,78 @@ __global__ __launch_bounds__(kFinThreads) void elastic_finish_kernel(int R, int 
 }
 
 // -------------------------------------------------------------- select ----
-__global__ __launch_bounds__(kSelThreads) void elastic_select_kernel(
-    const int32_t* __restrict__ cand_offsets, int R, int N, GateScoreBufs sb, ElasticWs ew,
-    uint8_t* __restrict__ selected, int32_t* status) {
-  extern __shared__ int32_t s_offs[];  // R + 1 entries
-  for (int i = threadIdx.x; i <= R; i += kSelThreads) s_offs[i] = cand_offsets[i];
+// The grants of R <= kSelThreads requests, request tid on thread tid: as
+// elastic_finish, kept in LDS (cut in s_cut, g1 and g2 per request).
+__device__ __forceinline__ int own_grants(int R, int budget, const ElasticWs& ew, int32_t* s_g1,
+                                          int32_t* s_g2, int32_t* num_selected,
+                                          int32_t* trunc_out, bool first) {
+  constexpr int NW = kSelThreads / kWave;
+  __shared__ int s_part[NW][kSlots];
+  __shared__ int s_scan[NW + 1];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+  const int tdep = tid < R ? ew.tdep[tid] : kNone;
+  const int w2 = tid < R ? ew.w2[tid] : 0;
+  int dem[kSlots];
+#pragma unroll
+  for (int d = 1; d < kSlots; ++d) dem[d] = tid < R ? ew.dem[size_t(tid) * kSlots + d] : 0;
+#pragma unroll
+  for (int d = 1; d < kSlots; ++d) {
+    const int v = int(wave_sum(uint32_t(dem[d])));
+    if (lane == 0) s_part[wid][d] = v;
+  }
   __syncthreads();
+  // lane d - 1 of every wave holds the demand of depth d; the depth loop of phase 1
+  // runs while budget is left (see elastic_finish)
+  int col = 0;
+  if (lane < ECHO_MAX_DEPTH)
+#pragma unroll
+    for (int w = 0; w < NW; ++w) col += s_part[w][lane + 1];
+  int left = budget, cut = kNone;
+#pragma unroll
+  for (int d = 1; d <= ECHO_MAX_DEPTH; ++d) {
+    const int Td = __builtin_amdgcn_readlane(col, d - 1);
+    if (cut == kNone) {
+      if (Td >= left) cut = d;
+      else left -= Td;
+    }
+  }
+  const bool phase1 = cut <= ECHO_MAX_DEPTH;
+  int v = w2;
+  if (phase1) {
+#pragma unroll
+    for (int d = 1; d < kSlots; ++d) v = d == cut ? dem[d] : v;
+  }
+  int tot;
+  const int excl = block_exclusive_sum<kSelThreads>(v, s_scan, &tot);
+  const int grant = max(0, min(v, left - excl));
+  if (tid < R) {
+    s_g1[tid] = phase1 ? grant : 0;
+    s_g2[tid] = phase1 ? 0 : grant;
+    if (first && trunc_out != nullptr)
+      trunc_out[tid] = !phase1 || tdep < cut || (tdep == cut && excl < left) ? tdep : kNone;
+  }
+  if (first && tid == 0) *num_selected = phase1 ? budget : budget - (left - min(tot, left));
+  __syncthreads();
+  return cut;
+}
+
+// kOwn: R <= kSelThreads, the grants are found here; else elastic_finish has.
+template <bool kOwn>
+__global__ __launch_bounds__(kSelThreads) void elastic_select_kernel(
+    const int32_t* __restrict__ cand_offsets, int R, int N, int budget, GateScoreBufs sb,
+    ElasticWs ew, uint8_t* __restrict__ selected, int32_t* __restrict__ num_selected,
+    int32_t* __restrict__ trunc_out, int32_t* status) {
+  extern __shared__ int32_t s_offs[];  // R + 1 entries
+  __shared__ int32_t s_g1[kOwn ? kSelThreads : 1], s_g2[kOwn ? kSelThreads : 1];
+  for (int i = threadIdx.x; i <= R; i += kSelThreads) s_offs[i] = cand_offsets[i];
   const int g = blockIdx.x * kSelThreads + threadIdx.x;
-  const int cut = ew.meta[0];
+  int cut;
+  if (kOwn) {
+    cut = own_grants(R, budget, ew, s_g1, s_g2, num_selected, trunc_out, blockIdx.x == 0);
+  } else {
+    __syncthreads();
+    cut = ew.meta[0];
+  }
   // the selection rule, with each round of independent loads issued together
   auto is_sel = [&](int x) -> bool {
     const uint32_t key = sb.keys[x];
@@ -480,8 +654,8 @@ __global__ __launch_bounds__(kSelThreads) void elastic_select_kernel(
     if (key == 0u || rk < 0) return false;  // also every candidate of a malformed CSR
     const int r = upper_bound_idx(s_offs, R + 1, x);
     const int dm = ew.dem[size_t(r) * kSlots + d];  // d <= 16: the key is finite
-    const int a = ew.g1[r];
-    const int b = ew.g2[r];
+    const int a = kOwn ? s_g1[r] : ew.g1[r];
+    const int b = kOwn ? s_g2[r] : ew.g2[r];
     const int td = ew.tdep[r];
     if (d < cut && rk < dm) return true;
     if (d == cut && rk < a) return true;
@@ -521,20 +695,23 @@ int32_t launch_gate_elastic(const int32_t* cand_offsets, const int32_t* parent, 
   }
   ea.w_topk = w_topk;
   ea.w_max = w_max;
-  GateScoreBufs sb;
-  if (launch_gate_score(cand_offsets, parent, logq, R, N, path_score, workspace, status, stream,
-                        &sb) != ECHO_OK)
-    return ECHO_ERR_HIP;
+  const GateWs gws = gate_ws_layout(workspace, N, R);
+  const ElasticPool ep{parent, logq, path_score, gws.keys, gws.pglob, gws.depth};
+  const GateScoreBufs sb{gws.keys, gws.pglob, gws.depth};
   char* own = static_cast<char*>(workspace) + el_align(gate_workspace_bytes(R, N, budget));
   const ElasticWs ew = elastic_ws_layout(own, R, N);
-  hipLaunchKernelGGL(elastic_request_kernel, dim3(R), dim3(kElThreads), 0, stream, cand_offsets,
-                     N, sb, ea, ew);
-  hipLaunchKernelGGL(elastic_finish_kernel, dim3(1), dim3(kFinThreads), 0, stream, R, budget, ew,
-                     num_selected, trunc_depth);
-  if (N > 0)
-    hipLaunchKernelGGL(elastic_select_kernel, dim3((N + kSelThreads - 1) / kSelThreads),
-                       dim3(kSelThreads), size_t(R + 1) * sizeof(int32_t), stream, cand_offsets,
-                       R, N, sb, ew, selected, status);
+  hipLaunchKernelGGL(elastic_request_kernel, dim3(R), dim3(kElThreads), 0, stream, cand_offsets, R,
+                     N, ep, ea, ew, status);
+  const bool own_grants_fit = R <= kSelThreads;
+  if (!own_grants_fit)
+    hipLaunchKernelGGL(elastic_finish_kernel, dim3(1), dim3(kFinThreads), 0, stream, R, budget, ew,
+                       num_selected, trunc_depth);
+  const int blocks = (N + kSelThreads - 1) / kSelThreads;
+  if (blocks > 0 || own_grants_fit)  // (without candidates: the grants' outputs only)
+    hipLaunchKernelGGL(own_grants_fit ? elastic_select_kernel<true> : elastic_select_kernel<false>,
+                       dim3(blocks > 0 ? blocks : 1), dim3(kSelThreads),
+                       size_t(R + 1) * sizeof(int32_t), stream, cand_offsets, R, N, budget, sb, ew,
+                       selected, num_selected, trunc_depth, status);
   return hipGetLastError() == hipSuccess ? ECHO_OK : ECHO_ERR_HIP;
 }
 

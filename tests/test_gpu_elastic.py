@@ -48,6 +48,12 @@ def run_elastic(offs, parent, logq, budget, sig, log_tau, w_topk, w_max):
                 trunc_depth=trunc.cpu().numpy())
 
 
+def run_elastic_offsets(offs, parent, logq, N):
+    """run_elastic on offsets that need not describe the N candidates."""
+    assert int(offs[-1]) == N
+    return run_elastic(offs, parent, logq, 50, [2], [-0.5], 2, 4)
+
+
 def check(offs, parent, logq, budget, sig, log_tau, w_topk, w_max):
     lt = np.asarray(log_tau, np.float32)
     ref = oracle.elastic_schedule(offs, parent, logq, budget, list(sig), lt, w_topk, w_max)
@@ -159,3 +165,30 @@ def test_full_step_with_elastic_gate():
     gc.compare_front(res, dict(gate=g, mask=m, accept=a), int(b["cand_offsets"][-1]))
     assert np.array_equal(res["trunc_depth"], g["trunc_depth"])
     gc.compare_attn(res["out"], res["lse"], ro, rl, range(m["num_slots"]))
+
+
+@pytest.mark.parametrize("R", [1, 1024, 1025])
+def test_request_and_grant_edges(R):
+    """Requests on both sides of what one pass of the scores takes (1024
+    candidates) and of what LDS takes (4096), with chains deeper than the depth
+    limit across them, and request counts on both sides of what the select
+    launch grants by itself (1024)."""
+    rng = np.random.default_rng(R)
+    sizes = np.full(R, 2)
+    big = [1023, 1024, 1025, 3000, 4096, 4097][:R]
+    sizes[rng.permutation(R)[:len(big)]] = big
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    local = np.concatenate([np.arange(k) for k in sizes])
+    # every 97th node starts a chain of its successors, the rest are shallow
+    chain = (local % 97 > 0) & (local % 97 < 25)
+    parent = np.where(chain, local - 1, np.where(local % 3 == 0, -1, local // 200 - 1))
+    N = int(offs[-1])
+    logq = rng.choice(np.array([0.0, -0.25, -0.5, -1.0], np.float32), N)
+    for budget, wt, wm in [(300, 2, 5), (5000, 40, 200)]:
+        _log(f"[elastic] edges R={R} N={N} B={budget}")
+        check(offs, parent.astype(np.int32), logq, budget, [2, 4], [-0.9, -1.6], wt, wm)
+    bad = offs.copy()
+    bad[0] = 1  # malformed: nothing is scored or selected
+    got = run_elastic_offsets(bad, parent.astype(np.int32), logq, N)
+    assert got["status"] & 128 and got["num_selected"] == 0 and not got["selected"].any()
+    assert np.all(np.isneginf(got["path_score"]))
