@@ -255,12 +255,17 @@ __device__ int staged_scores(int lo, int n, const ElasticPool& ep, ElasticLds& L
       if (!__syncthreads_or(open != 0u)) break;
       uint64_t v[kPer];
 #pragma unroll
-      for (int q = 0; q < kPer; ++q) v[q] = ((open >> q) & 1u) ? L.word[pp[q]] : kUnknown;
+      for (int q = 0; q < kPer; ++q)  // (a parent may be scored in this very round: either word will do)
+        v[q] = ((open >> q) & 1u) ? __hip_atomic_load(&L.word[pp[q]], __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_WORKGROUP)
+                                  : kUnknown;
 #pragma unroll
       for (int q = 0; q < kPer; ++q) {
         if (uint32_t(v[q]) == kUnknown || uint32_t(v[q] >> 32) >= ECHO_MAX_DEPTH) continue;
         const float s = __uint_as_float(uint32_t(v[q])) + lq[q];
-        L.word[i0 + tid + q * kElThreads] = (((v[q] >> 32) + 1) << 32) | __float_as_uint(s);
+        __hip_atomic_store(&L.word[i0 + tid + q * kElThreads],
+                           (((v[q] >> 32) + 1) << 32) | uint64_t(__float_as_uint(s)),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         open &= ~(1u << q);
       }
     }

@@ -148,7 +148,7 @@ __device__ int select_small(const FrontArgs& a, const SmallPool& in, const int32
   // binary32 adds in the same order as a walk from the root.  (Short code: with the
   // instruction cache cold, an unrolled walk per node cost more than the launches
   // it saved.)
-  uint2* s_node = reinterpret_cast<uint2*>(smem);
+  uint64_t* s_node = reinterpret_cast<uint64_t*>(smem);  // depth above, score below
   uint32_t* s_key = reinterpret_cast<uint32_t*>(smem);  // replaces them
   constexpr uint32_t kUnknown = 0x7FFFFFFFu;
   const int n = a.N;
@@ -169,11 +169,11 @@ __device__ int select_small(const FrontArgs& a, const SmallPool& in, const int32
     else if (lq[k] > 0.0f) { *bits |= ECHO_DATA_POS_LOGQ; lq[k] = 0.0f; }
     if (p < 0) {
       sc[k] = 0.0f + lq[k];
-      s_node[g] = make_uint2(__float_as_uint(sc[k]), 1u);
+      s_node[g] = (uint64_t(1) << 32) | __float_as_uint(sc[k]);
     } else {
       par[k] = lo + p;
       open |= 1u << k;
-      s_node[g] = make_uint2(kUnknown, 0u);
+      s_node[g] = kUnknown;
     }
   }
   for (int i = tid; i < 512; i += kGateThreads) (&s_rl.h[0][0])[i] = 0u;
@@ -183,10 +183,14 @@ __device__ int select_small(const FrontArgs& a, const SmallPool& in, const int32
 #pragma unroll
     for (int k = 0; k < kSmallPer; ++k) {
       if (!((open >> k) & 1u)) continue;
-      const uint2 v = s_node[par[k]];
-      if (v.x == kUnknown || v.y >= ECHO_MAX_DEPTH) continue;
-      sc[k] = __uint_as_float(v.x) + lq[k];
-      s_node[k * kFrontThreads + tid] = make_uint2(__float_as_uint(sc[k]), v.y + 1u);
+      // (a parent may be scored in this very round: either word will do)
+      const uint64_t v =
+          __hip_atomic_load(&s_node[par[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (uint32_t(v) == kUnknown || uint32_t(v >> 32) >= ECHO_MAX_DEPTH) continue;
+      sc[k] = __uint_as_float(uint32_t(v)) + lq[k];
+      __hip_atomic_store(&s_node[k * kFrontThreads + tid],
+                         (((v >> 32) + 1) << 32) | uint64_t(__float_as_uint(sc[k])),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       open &= ~(1u << k);
     }
   }
