@@ -1,5 +1,6 @@
 // Gate: path scores (eq. 5) and the global top-B selection under the batch
-// verification cap (eq. 4).  Three launches, none of which contends on a
+// verification cap (eq. 4).  One launch for a small pool (gate_small), else three,
+// none of which contends on a
 // global atomic (on a multi-XCD part those serialise far from the CUs):
 //
 //   gate_score   one thread per candidate: root->leaf binary32 fold of the path
@@ -403,6 +404,31 @@ __global__ __launch_bounds__(kGateThreads) void gate_finish_kernel(int N, int nb
   gate_finish_body(N, nblocks, ws, selected, status, FinishLds{s_k, s_g, s_base});
 }
 
+// The whole gate of a small pool in one launch of one workgroup.  The three launches
+// are chains of round trips whatever N is, this one's search grows with N.  Three
+// launches -> one: 9.2 -> 5.2 us at 208 candidates, 10.9 -> 7.8 at 1280, 11.5 -> 9.4 at
+// 2560 (32 requests), 12.0 -> 10.3 at 2400 (16 requests); beyond kSmallPool candidates a
+// thread would hold a fourth one, and the two meet.
+static_assert((2 * kSmallPool + ECHO_MAX_REQUESTS + 1) * 4 <= 48 * 1024, "LDS of gate_small");
+__global__ __launch_bounds__(kGateThreads) void gate_small_kernel(
+    const int32_t* __restrict__ cand_offsets, SmallGate a, int32_t* status) {
+  extern __shared__ __attribute__((aligned(16))) int32_t smem[];  // 2 N words, R + 1 offsets
+  const SmallPool pool = load_small(a);
+  int32_t* offs = smem + 2 * a.N;
+  for (int i = threadIdx.x; i <= a.R; i += kGateThreads) offs[i] = cand_offsets[i];
+  __syncthreads();
+  // the candidate CSR must be well formed before anything is read through it
+  bool bad = threadIdx.x == 0 && (offs[0] != 0 || offs[a.R] != a.N);
+  for (int r = threadIdx.x; r < a.R; r += kGateThreads) bad = bad || offs[r + 1] < offs[r];
+  const bool ok = !__syncthreads_or(bad);
+  int bits = !ok && threadIdx.x == 0 ? ECHO_DATA_BAD_OFFSETS : 0;
+  select_small(a, pool, offs, ok, true, smem, &bits, [&](auto sel) {
+    for (int i = threadIdx.x; i < a.N; i += kGateThreads) sel(i);
+    return 0;
+  });
+  wave_status_or(status, bits);
+}
+
 }  // namespace
 
 namespace {
@@ -430,6 +456,12 @@ int32_t launch_gate_impl(const int32_t* cand_offsets, const int32_t* parent, con
     sp.mask |= 1u << d;
   }
   sp.trunc_out = trunc_depth;
+  if (!sp.enabled && finish && N <= kSmallPool) {
+    const SmallGate a{N, R, budget, parent, logq, path_score, selected, num_selected};
+    hipLaunchKernelGGL(gate_small_kernel, dim3(1), dim3(kGateThreads),
+                       (size_t(2) * N + R + 1) * sizeof(int32_t), stream, cand_offsets, a, status);
+    return hipGetLastError() == hipSuccess ? ECHO_OK : ECHO_ERR_HIP;
+  }
   if (sp.enabled) {
     const int n = R * kDepths;
     hipLaunchKernelGGL(gate_lmax_clear_kernel, dim3((n + kGateThreads - 1) / kGateThreads),

@@ -393,5 +393,140 @@ __device__ void gate_finish_body(int N, int nblocks, const GateWs& ws,
 }
 
 
+// ---------------------------------------------------------- small pools ----
+// Candidates of a small pool, kSmallPer per thread: its whole top-B gate runs on one
+// workgroup, in LDS.  Whole fused steps over N candidates
+// (8 / 8 heads, 64 keys), lists -> small pool: 28.5 -> 23.3 us at 208, 32.1 -> 28.6
+// at 2080, 36.6 -> 34.7 at 3120, 38.7 -> 38.4 at 4160, 42.0 -> 44.7 at 6136 (one
+// workgroup's searches and histogram rounds grow with N).
+constexpr int kSmallPer = 3;
+constexpr int kSmallPool = kSmallPer * kGateThreads;
+
+// What a small pool's gate reads and writes.
+struct SmallGate {
+  int N, R, budget;
+  const int32_t* parent;
+  const float* logq;
+  float* path_score;  // nullable
+  uint8_t* selected;
+  int32_t* num_selected;
+};
+
+// A small pool's candidates in registers, loaded before anything waits.
+struct SmallPool {
+  int32_t par[kSmallPer];
+  float lq[kSmallPer];
+};
+
+__device__ __forceinline__ SmallPool load_small(const SmallGate& a) {
+  SmallPool p;
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int g = k * kGateThreads + int(threadIdx.x);
+    p.par[k] = g < a.N ? a.parent[g] : -1;
+    p.lq[k] = g < a.N ? a.logq[g] : 0.0f;
+  }
+  return p;
+}
+
+// The whole top-B gate of a small pool; finish(sel): the caller's pass over the
+// candidates, sel(i) says whether candidate i is selected and, if `first`, writes its
+// flag.  offs: the candidate offsets in LDS, ok: they are well formed; smem: 8 bytes
+// per candidate.
+template <typename Finish>
+__device__ __forceinline__ auto select_small(const SmallGate& a, const SmallPool& in,
+                                             const int32_t* offs, bool ok, bool first,
+                                             int32_t* smem, int* bits, Finish finish) {
+  __shared__ RadixLds s_rl;
+  __shared__ uint32_t s_fin[kGateThreads / kWave];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  // Scores top-down, all nodes of a depth in one round: (score, depth) of every node
+  // whose score is known, a NaN score where it is not.  A node folds the same
+  // binary32 adds in the same order as a walk from the root.  (Short code: with the
+  // instruction cache cold, an unrolled walk per node cost more than the launches
+  // it saved.)
+  uint64_t* s_node = reinterpret_cast<uint64_t*>(smem);  // depth above, score below
+  uint32_t* s_key = reinterpret_cast<uint32_t*>(smem);  // replaces them
+  constexpr uint32_t kUnknown = 0x7FFFFFFFu;
+  const int n = a.N;
+  int par[kSmallPer];
+  float lq[kSmallPer], sc[kSmallPer];
+  uint32_t open = 0u;  // bit k: the thread's node k has no score yet
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int g = k * kGateThreads + tid;
+    sc[k] = -__builtin_inff();
+    lq[k] = in.lq[k];
+    par[k] = -1;
+    if (!ok || g >= n) continue;
+    const int lo = offs[upper_bound_idx(offs, a.R + 1, g)];
+    int p = in.par[k];
+    if (p < -1 || p >= g - lo) { *bits |= ECHO_DATA_BAD_PARENT; p = -1; }
+    if (lq[k] != lq[k]) { *bits |= ECHO_DATA_NAN_LOGQ; lq[k] = -__builtin_inff(); }
+    else if (lq[k] > 0.0f) { *bits |= ECHO_DATA_POS_LOGQ; lq[k] = 0.0f; }
+    if (p < 0) {
+      sc[k] = 0.0f + lq[k];
+      s_node[g] = (uint64_t(1) << 32) | __float_as_uint(sc[k]);
+    } else {
+      par[k] = lo + p;
+      open |= 1u << k;
+      s_node[g] = kUnknown;
+    }
+  }
+  for (int i = tid; i < 512; i += kGateThreads) (&s_rl.h[0][0])[i] = 0u;
+  // after ECHO_MAX_DEPTH - 1 rounds every node of depth <= ECHO_MAX_DEPTH is known
+  for (int round = 1; round < ECHO_MAX_DEPTH; ++round) {
+    if (!__syncthreads_or(open != 0u)) break;
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k) {
+      if (!((open >> k) & 1u)) continue;
+      // (a parent may be scored in this very round: either word will do)
+      const uint64_t v =
+          __hip_atomic_load(&s_node[par[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (uint32_t(v) == kUnknown || uint32_t(v >> 32) >= ECHO_MAX_DEPTH) continue;
+      sc[k] = __uint_as_float(uint32_t(v)) + lq[k];
+      __hip_atomic_store(&s_node[k * kGateThreads + tid],
+                         (((v >> 32) + 1) << 32) | uint64_t(__float_as_uint(sc[k])),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      open &= ~(1u << k);
+    }
+  }
+  if (open != 0u) *bits |= ECHO_DATA_TOO_DEEP;  // deeper: their scores stay -inf
+  uint32_t key[kSmallPer];
+  uint32_t fin = 0u;
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int g = k * kGateThreads + tid;
+    key[k] = score_key(sc[k]);
+    if (first && g < n && a.path_score != nullptr) a.path_score[g] = sc[k];
+    fin += uint32_t(__popcll(__ballot(key[k] != 0u)));
+  }
+  if (lane == 0) s_fin[tid / kWave] = fin;
+  __syncthreads();  // every score has been read
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int g = k * kGateThreads + tid;
+    if (g < n) s_key[g] = key[k];
+  }
+  fin = 0u;
+#pragma unroll
+  for (int w = 0; w < kGateThreads / kWave; ++w) fin += s_fin[w];
+  const uint32_t m = min(uint32_t(a.budget), fin);
+  if (first && tid == 0) *a.num_selected = int32_t(m);
+  __syncthreads();
+  uint32_t tk = 0xFFFFFFFFu;
+  int32_t tg = -1;
+  if (m != 0u)
+    find_threshold(RadixSel{0u, 32, m, fin}, n, n, [&](int i) { return s_key[i]; },
+                   [](int i) { return int32_t(i); }, s_rl, &tk, &tg);
+  const auto sel = [&](int i) {
+    const uint32_t k = s_key[i];
+    const bool on = m != 0u && k != 0u && (k > tk || (k == tk && i <= tg));
+    if (first) a.selected[i] = on ? 1 : 0;
+    return on;
+  };
+  return finish(sel);
+}
+
 }  // namespace
 }  // namespace echo

@@ -139,6 +139,29 @@ def test_all_equal_scores_large_tie_class():
         _check_all(b, attention=(budget == 241))
 
 
+@pytest.mark.parametrize("n,R,budget", [(0, 3, 4), (1, 1, 1), (1025, 9, 64), (3071, 40, 300),
+                                        (3072, 1, 3072), (3073, 40, 300), (3000, 4095, 200)])
+def test_small_pool_gate(n, R, budget):
+    """Around the size up to which the gate is one launch (3072 candidates): ties, scores
+    of -inf, bad parents, NaN and chains past the depth cap."""
+    rng = np.random.default_rng(n + R)
+    offs = np.concatenate([[0], np.sort(rng.integers(0, n + 1, R - 1)), [n]]).astype(np.int32)
+    local = np.concatenate([np.arange(k) for k in np.diff(offs)]).astype(np.int64)
+    parent = np.where(rng.random(n) < 0.3, -1, np.where(rng.random(n) < 0.2, local - 1,
+                                                        (local - 1) // 2)).astype(np.int32)
+    logq = rng.choice(np.array([0.0, -0.25, -0.5, -1.0, -3.0, -np.inf], np.float32), n)
+    if n > 1000:
+        parent[rng.integers(0, n, 3)] = 5000
+        logq[rng.integers(0, n, 3)] = np.nan
+        r = int(np.argmax(np.diff(offs)))
+        if offs[r + 1] - offs[r] > 30:
+            parent[offs[r]:offs[r] + 20] = np.arange(-1, 19)
+    pool = dict(cand_offsets=offs, parent=parent, token=rng.integers(0, 5, n).astype(np.int32),
+                logq=logq, root_token=rng.integers(0, 5, R).astype(np.int32))
+    print(f"[edges] small pool N={n} R={R} B={budget}", flush=True)
+    _check_all(make_micro_batch(pool, budget, hq=2, hkv=2, p_range=(0, 8), seed=n), attention=False)
+
+
 def test_crowded_threshold_bin():
     """20k distinct path scores inside one 11-bit key bin: the threshold is found
     over more keys than the finish kernel gathers into LDS, and at budgets whose
