@@ -1,6 +1,6 @@
 // Tree-masked grouped-query verification attention (one verification forward
-// over the flattened super-tree).  Three launches (a paged cache adds
-// attn_pages first, which checks the block tables' page ids):
+// over the flattened super-tree).  Three launches (a paged cache with large block
+// tables adds attn_pages first, which checks their page ids):
 //
 //   attn_plan     one workgroup.  A stream is one KV head of one request
 //                 together with a pass over its rows (rows = verify slots x
@@ -62,11 +62,64 @@ __global__ __launch_bounds__(kPageChunk) void attn_pages_kernel(KvSource kv) {
   if (threadIdx.x == 0) const_cast<int32_t*>(kv.page_bad)[size_t(r) * kv.page_chunks + c] = bad;
 }
 
+// The plan's own page check: block tables of up to kOwnPages entries (R rows, one
+// request per thread).  Their loads, 16 per thread in flight, are issued with those of
+// the requests' fields, where attn_pages costs a launch (3.1 us) and the read of its
+// flags.  Every row's max_pages entries are read; those past the prefix don't count.
+// Whole calls over small caches, attn_pages -> own check: 18.0 -> 16.9 us (32 rows of
+// 32 entries), 19.7 -> 18.7 (64 of 16), 34.5 -> 33.5 (256 of 4); at 4096 entries 18.1 ->
+// 17.7, 19.7 -> 19.5, 34.6 -> 34.4; at 8192 (a second batch) 18.1 -> 19.6, 34.5 -> 36.2.
+// Hence one batch.
+constexpr int kOwnBatch = 16;  // page ids per thread
+constexpr int kOwnPages = kOwnBatch * kThreads;
+
+__host__ __device__ inline bool plan_checks_pages(int R, int max_pages) {
+  return R <= kThreads && (long long)R * max_pages <= kOwnPages;
+}
+
+__device__ __forceinline__ void own_page_check(const KvSource& kv, int R, const RequestIn& in,
+                                               int32_t* s_np, int32_t* s_bad) {
+  const int tid = threadIdx.x;
+  const int mp = kv.max_pages, total = R * mp;
+  int pg[kOwnBatch];
+#pragma unroll
+  for (int k = 0; k < kOwnBatch; ++k) pg[k] = kv.block_table[min(tid + k * kThreads, total - 1)];
+  const bool len_ok = in.P >= 0 && in.P <= (long long)mp * kv.page_size;
+  s_np[tid] = tid < R && len_ok ? int((in.P + kv.page_size - 1) / kv.page_size) : 0;
+  s_bad[tid] = 0;
+  __syncthreads();
+  // entry tid + 256 k is page c of request r, stepped without a division
+  const int dr = kThreads / mp, dc = kThreads % mp;
+  int r = tid / mp, c = tid % mp;
+#pragma unroll
+  for (int k = 0; k < kOwnBatch; ++k) {
+    if (r < R && (pg[k] < 0 || pg[k] >= kv.num_pages) && c < s_np[r]) s_bad[r] = 1;
+    r += dr;
+    c += dc;
+    if (c >= mp) {
+      c -= mp;
+      ++r;
+    }
+  }
+  __syncthreads();
+}
+
 template <bool kWide>
 __global__ __launch_bounds__(kThreads) void attn_plan_kernel(
     const int32_t* __restrict__ q_offsets, KvSource kv, int R, int hkv, int G, int max_rows,
     int nb, long long ucap, AttnWs ws, int32_t* status) {
   extern __shared__ int32_t plan_tables[];  // plan_table_words(min(R, kThreads))
+  __shared__ int32_t s_np[kThreads], s_bad[kThreads];
+  if (kv.block_table != nullptr && kv.page_bad == nullptr) {
+    RequestIn in = {};
+    if (int(threadIdx.x) < R) in = load_request(q_offsets, kv, threadIdx.x);
+    own_page_check(kv, R, in, s_np, s_bad);
+    kv.page_bad = s_bad;
+    kv.page_chunks = 1;
+    plan_body<kThreads, kWide>(q_offsets, kv, R, hkv, G, max_rows, nb, ucap, ws, status,
+                               plan_tables, &in);
+    return;
+  }
   plan_body<kThreads, kWide>(q_offsets, kv, R, hkv, G, max_rows, nb, ucap, ws, status, plan_tables);
 }
 
@@ -849,7 +902,7 @@ int32_t launch_attn_impl(const AttnArgs& a, bool plan, bool combine, hipStream_t
   kv.num_pages = static_cast<long long>(a.num_pages);
   kv.page_bad = nullptr;
   kv.page_chunks = 0;
-  if (plan && a.block_table != nullptr) {
+  if (plan && a.block_table != nullptr && !plan_checks_pages(a.R, a.max_pages)) {
     // the flags borrow the start of the partials, which the main kernel only
     // writes later on the same stream
     kv.page_chunks = (a.max_pages + kPageChunk - 1) / kPageChunk;

@@ -218,7 +218,7 @@ struct KvSource {
   int page_size;
   int max_pages;
   long long num_pages;
-  const int32_t* page_bad;  // [R][page_chunks]: written by attn_pages, read by the plan
+  const int32_t* page_bad;  // [R][page_chunks]: flags of attn_pages (or the plan's own check)
   int page_chunks;
 };
 

@@ -125,6 +125,52 @@ def test_paged_attention_missing_page_skips_the_request():
     gc.compare_attn(out, lse, ro, rl, rows)
 
 
+@pytest.mark.parametrize("R,max_pages", [(1, 1), (1, 4096), (1, 4097), (3, 1365), (3, 1366),
+                                         (256, 16), (256, 17), (257, 15)])
+def test_paged_attention_page_check_sizes(R, max_pages):
+    """Around the size up to which the plan checks the page ids itself: a bad id in the
+    table's very last entry, a length past the table row, ids past the prefix that don't
+    count."""
+    import types
+    S = 32
+    rng = np.random.default_rng(R * 10007 + max_pages)
+    kp, vp = (synth.f32_to_bf16_bits(rng.standard_normal((40, S, 1, 128)).astype(np.float32))
+              for _ in range(2))
+    q, kn, vn = (synth.f32_to_bf16_bits(rng.standard_normal((R, 1, 128)).astype(np.float32))
+                 for _ in range(3))
+    cfg = types.SimpleNamespace(R=R, budget=0, hq=1, hkv=1, mask_words=1)
+    b = dict(cfg=cfg, q=q, k_new=kn, v_new=vn, sm_scale=128 ** -0.5)
+    m = dict(q_offsets=np.arange(R + 1, dtype=np.int32),
+             tree_mask=np.ones((R, 1), np.uint32))
+    plen = rng.integers(0, min(max_pages, 6) * S + 1, R).astype(np.int32)
+    plen[-1] = max_pages * S - 5
+    bt = rng.integers(0, 40, (R, max_pages)).astype(np.int32)
+    for r in range(R):
+        bt[r, (plen[r] + S - 1) // S:] = -1 if r % 2 else 40
+    for spoil in ("none", "last id", "length"):
+        t, n = bt.copy(), plen.copy()
+        skipped = -1
+        if spoil == "last id":
+            skipped = R - 1
+            t[skipped, -1] = 40
+        elif spoil == "length":
+            skipped = R // 2
+            n[skipped] = max_pages * S + 1
+        _log(f"[serve] page check R={R} max_pages={max_pages} spoil={spoil}")
+        out, lse, status = run_paged(b, m, kp, vp, t, n, S)
+        assert status == (0 if skipped < 0 else oracle.status.BAD_OFFSETS)
+        rows = [s for s in (range(R) if R <= 3 else (0, 1, R // 2, R - 2, R - 1)) if s != skipped]
+        assert skipped < 0 or np.all(np.isnan(out[skipped]))
+        assert not np.any(np.isnan(np.delete(out, [skipped], 0) if skipped >= 0 else out))
+        if not rows:
+            continue
+        if skipped >= 0:
+            n[skipped] = 0  # (the oracle is given the valid requests)
+        ro, rl, _ = oracle.tree_verify_attn_paged(q, kn, vn, kp, vp, t, n, S, m["q_offsets"],
+                                                  m["tree_mask"], 1, 1, b["sm_scale"], rows=rows)
+        gc.compare_attn(out, lse, ro, rl, rows)
+
+
 def _accept_logits_case(b, m, vocab, rng, ties=True, nan_rows=0):
     import torch
     import paper_2604_09603_amd as pkg
