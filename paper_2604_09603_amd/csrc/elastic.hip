@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kFinThreads) void elastic_finish_kernel(int R, int 
 
 // -------------------------------------------------------------- select ----
 // The grants of R <= kSelThreads requests, request tid on thread tid: as
-// elastic_finish, kept in LDS (cut in s_cut, g1 and g2 per request).
+// elastic_finish, kept in LDS (g1 and g2 per request).  Returns the cut depth.
 __device__ __forceinline__ int own_grants(int R, int budget, const ElasticWs& ew, int32_t* s_g1,
                                           int32_t* s_g2, int32_t* num_selected,
                                           int32_t* trunc_out, bool first) {
