@@ -199,7 +199,7 @@ def pmc_summary(args):
     if "hbm_bytes_per_launch" in out:
         lines += [f"| hbm_bytes_per_launch | {out['hbm_bytes_per_launch'] / 1e9:.4f} GB |"]
     lines += ["", "Normalisation: " + " ".join(pmc_summary.__doc__.split("Normalisation: ")[1].split()),
-              "", f"sha256 of attn.hip + attn_device.h + build.py at measurement: `{out['attn_src_sha256']}`", ""]
+              "", f"sha256 of the attention sources + build.py at measurement: `{out['attn_src_sha256']}`", ""]
     with open(args.pmc_out + ".md", "w") as f:
         f.write("\n".join(lines))
     log(f"wrote {args.pmc_out}.json and .md")
