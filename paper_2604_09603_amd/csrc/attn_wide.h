@@ -217,7 +217,9 @@ __device__ __forceinline__ void wide_scores(uint32_t stg, uint32_t ka, const bf1
 }
 
 // The softmax of those scores and O^T += V^T P^T.  masked: key k of tile j is visible
-// to the lane's row iff bit k of word[j].  A wave's vector instructions overlap with
+// to the lane's row iff bit k of word[j].  one (NT == 2): the second tile is the
+// repeated one of an odd segment, with no visible key; its products are left out, as 0
+// times an infinite value is NaN.  A wave's vector instructions overlap with
 // only the last third of a matrix product, and a result is ready two issue slots
 // after its instruction: the products of P V are spread between the exponentials of
 // the next 16 keys, and maxima and sums run in independent chains.  Fences
@@ -226,7 +228,8 @@ __device__ __forceinline__ void wide_scores(uint32_t stg, uint32_t ka, const bf1
 template <int NT>
 __device__ __forceinline__ void wide_values(uint32_t stg, uint32_t va, floatx16 (&s)[NT],
                                             floatx16 (&o)[4], WideRow& rs, bool masked,
-                                            float scale2, const uint32_t (&word)[NT]) {
+                                            bool one, float scale2,
+                                            const uint32_t (&word)[NT]) {
   const int h = (threadIdx.x & (kWave - 1)) >> 5;
   constexpr int NG = 2 * NT;  // groups of 16 keys
   va += stg;
@@ -295,6 +298,7 @@ __device__ __forceinline__ void wide_values(uint32_t stg, uint32_t va, floatx16 
   for (int i = 0; i < 4; ++i) two(0, i);
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
+    if (g == 2 && one) break;  // uniform
     const bf16x8 pf = as_bf16x8(make_uint4(pk[g][0], pk[g][1], pk[g][2], pk[g][3]));
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) {
@@ -320,6 +324,7 @@ __device__ __forceinline__ void wide_values(uint32_t stg, uint32_t va, floatx16 
       };
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
+        if (g == 2 && one) break;
         uint32_t pl[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -536,7 +541,7 @@ attn_wide_kernel(MainArgs a, AttnWs ws) {
         // the ones before
         sync();
         if (sent < known && sent < pos + kWideStages) send();
-        if (!active) continue;
+        if (!active || t + mine >= seg_hi) continue;
         const uint32_t stg = lds0 + uint32_t(((pos + mine) & (kWideStages - 1)) * kWideStageBytes);
         floatx16 s[NT];
         wide_scores<NT>(stg, ka, qf, s);
@@ -545,7 +550,7 @@ attn_wide_kernel(MainArgs a, AttnWs ws) {
         const bool masked = tt < full_lo || tt + NT > full_hi;
 #pragma unroll
         for (int j = 0; j < NT; ++j) word[j] = masked ? tile_word(tt + j) : 0u;
-        wide_values<NT>(stg, va, s, o, rs, masked, a.scale2, word);
+        wide_values<NT>(stg, va, s, o, rs, masked, t + 1 == seg_hi, a.scale2, word);
       }
     };
     if (by_key) {

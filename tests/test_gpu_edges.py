@@ -373,6 +373,52 @@ def test_wide_units_every_row(hq, hkv, page_size):
     assert np.array_equal(lse[:nq].view(np.uint32), res["lse"][:nq].view(np.uint32))
 
 
+@pytest.mark.parametrize("slots", [2, 3])
+@pytest.mark.parametrize("keys", [64, 96])
+def test_wide_units_infinite_value(slots, keys):
+    """A value of +inf (and one of -inf) at one key of the last tile of every request,
+    on the shared-ring kernel in its two forms (128 rows: two waves share the keys;
+    192: they do not), over an odd and an even number of tiles.  All logits are zero, so
+    every weight is the same: those dimensions are infinite in every row, the others are
+    the mean of the values, and nothing is NaN.  Two heads, one per workgroup: no row is
+    merged from partials."""
+    import torch
+    import paper_2604_09603_amd as pkg
+    from paper_2604_09603_amd.step import _aligned_workspace
+    R = torch.cuda.get_device_properties(0).multi_processor_count // 2
+    hq, hkv = 128, 2
+    rng = np.random.default_rng(keys + slots)
+    nq = R * slots
+    f32 = lambda a: torch.from_numpy(a.astype(np.float32)).to("cuda:0")  # noqa: E731
+    v = f32(rng.standard_normal((R, keys, hkv, 128))).bfloat16()
+    vn = f32(rng.standard_normal((R, slots, hkv, 128))).bfloat16()
+    v[:, keys - 5, :, 17] = float("inf")
+    v[:, keys - 31, :, 90] = float("-inf")
+    zeros = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda:0")  # noqa: E731
+    bits = lambda t: t.contiguous().view(torch.int16)  # noqa: E731
+    # slot j sees slots 0 .. j
+    mask = torch.from_numpy(np.tile((2 << np.arange(slots)) - 1, R).astype(np.int32)).to("cuda:0")
+    kvo = torch.arange(R + 1, dtype=torch.int64, device="cuda:0") * keys
+    qo = torch.arange(R + 1, dtype=torch.int32, device="cuda:0") * slots
+    out = torch.full((nq, hq, 128), 7.0, device="cuda:0")
+    ws = _aligned_workspace(pkg.tree_verify_attn_workspace_size(R, nq, hq, hkv), "cuda:0")
+    print(f"[edges] infinite values, {slots} slots, {keys} keys", flush=True)
+    pkg.echo_tree_verify_attn(bits(zeros(nq, hq, 128)), bits(zeros(nq, hkv, 128)), bits(vn),
+                              bits(zeros(R * keys, hkv, 128)), bits(v), kvo, R * keys, qo, mask, 1,
+                              R, nq, hq, hkv, 128, 1.0, out, None, ws)
+    torch.cuda.synchronize()
+    vd, nd = v.double().cpu().numpy(), vn.double().cpu().numpy()
+    got = out.double().cpu().numpy().reshape(R, slots, hkv, hq // hkv, 128)
+    for j in range(slots):
+        want = ((vd.sum(1) + nd[:, :j + 1].sum(1)) / (keys + j + 1))[:, :, None]
+        g = got[:, j]
+        assert np.all(g[..., 17] == np.inf) and np.all(g[..., 90] == -np.inf)
+        fin = np.isfinite(want[0, 0, 0])
+        assert fin.sum() == 126
+        # equal weights of exactly 1 / (keys + j + 1): only the order of fp32 sums
+        assert np.abs(g[..., fin] - want[..., fin]).max() <= 1e-5
+
+
 def _check_mask_only(b, offset):
     """echo_build_tree_mask on the oracle's selection stored `offset` bytes past a
     16-byte boundary: every output equal to the oracle's."""
