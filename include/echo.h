@@ -257,6 +257,13 @@ size_t echo_build_tree_mask_workspace_size(int32_t R, int32_t N, int32_t budget)
  * Requests with decreasing offsets, q_offsets beyond max_rows or kv_offsets
  * outside [0, kv_rows] are skipped (ECHO_DATA_BAD_OFFSETS); their rows are
  * not written.  Deterministic: no floating-point atomics.
+ * One of two kernels runs, which round differently (both within the precision
+ * above).  The choice follows num_kv_heads, the rows per KV head and request
+ * max_rows / R * Hq / Hkv and, up to 128 of these, kv_rows.  A paged call has no
+ * kv_rows and keeps the kernel for few rows there; otherwise the two calls
+ * give the same bits.  max_rows and kv_rows best state the batch at hand (the
+ * slots that exist, or R + budget) rather than what its arrays could hold: 32
+ * requests of one slot under a max_rows of 1024 take 5% longer.
  */
 int32_t echo_tree_verify_attn(const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new,
                               const uint16_t* k_cache, const uint16_t* v_cache,

@@ -82,8 +82,9 @@ def run_paged(b, m, kp, vp, bt, plen, page_size):
 @pytest.mark.parametrize("name,page_size", [("tiny", 32), ("tiny", 256), ("l8b", 64),
                                             ("l70b", 128), ("q235b", 64), ("long", 256)])
 def test_paged_attention_matches_contiguous(name, page_size):
-    """Same result as the contiguous GPU path (bit for bit: same tiles in the same
-    order) and within tolerance of the oracle."""
+    """Same result as the contiguous GPU path (bit for bit: these shapes run the same
+    kernel in both, over the same tiles in the same order) and within tolerance of the
+    oracle."""
     b = synth.make_batch(name, 0)
     ref = gc.oracle_front(b)
     m = ref["mask"]
@@ -104,6 +105,83 @@ def test_paged_attention_matches_contiguous(name, page_size):
                                               page_size, m["q_offsets"], m["tree_mask"], cfg.hq,
                                               cfg.hkv, b["sm_scale"], rows=rows)
     gc.compare_attn(out, lse, ro, rl, rows)
+
+
+# (Hq, Hkv, slots, keys as a function of the workgroups, same): few rows over one or
+# three KV heads, where the contiguous call's kv_rows decide which main kernel runs and
+# the paged call keeps the ordinary one; 128 rows; and more, where both take the
+# shared-ring kernel.  same: both calls run the same kernel
+POOL_CASES = [
+    (8, 1, 3, lambda nb: 900, True), (8, 1, 3, lambda nb: 32 * 32 * nb - 1, True),
+    (8, 1, 3, lambda nb: 64 * 32 * nb, False), (6, 3, 3, lambda nb: 32 * 32 * nb, False),
+    (64, 4, 8, lambda nb: 9000, False), (64, 4, 9, lambda nb: 9000, True),
+    (16, 4, 3, lambda nb: 9000, True)]
+
+
+@pytest.mark.parametrize("case", range(len(POOL_CASES)))
+def test_paged_attention_pool_size_does_not_matter(case):
+    """The pool and the table's rows may be any times larger than the prefixes without a
+    change of the result, with small tables (whose ids the plan checks) and large ones.
+    The contiguous call gives the same bits where it runs the same kernel, and the same
+    result to the bf16 weights' precision elsewhere."""
+    import torch
+    import paper_2604_09603_amd as pkg
+    from paper_2604_09603_amd.step import _aligned_workspace
+    hq, hkv, slots, total, same = POOL_CASES[case]
+    T = total(torch.cuda.get_device_properties(0).multi_processor_count)
+    R, S = 5, 256
+    rng = np.random.default_rng(case)
+    cuts = np.sort(rng.integers(0, T + 1, R - 1)) if T < 1 << 16 else np.arange(1, R) * (T // R) + 7
+    kvo = np.concatenate([[0], cuts, [T]]).astype(np.int64)
+    P = np.diff(kvo)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(case)
+    normal = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda:0").normal_(  # noqa: E731
+        generator=gen).view(torch.int16)
+    nq = R * slots
+    q, kn, vn = normal(nq, hq, 128), normal(nq, hkv, 128), normal(nq, hkv, 128)
+    kc, vc = normal(T, hkv, 128), normal(T, hkv, 128)
+    mask = _dev(np.tile((2 << np.arange(slots)) - 1, R).astype(np.int32))
+    qo = _dev(np.arange(R + 1, dtype=np.int32) * slots)
+    ws = _aligned_workspace(pkg.tree_verify_attn_workspace_size(R, nq, hq, hkv), "cuda:0")
+    new = lambda *s: torch.full(s, float("nan"), device="cuda:0")  # noqa: E731
+    ref, ref_lse = new(nq, hq, 128), new(nq, hq)
+    _log(f"[serve] pool size: {hq}/{hkv} heads, {T} keys")
+    pkg.echo_tree_verify_attn(q, kn, vn, kc, vc, _dev(kvo), T, qo, mask, 1, R, nq, hq, hkv, 128,
+                              0.088, ref, ref_lse, ws)
+    assert not torch.isnan(ref).any()
+    npg = (P + S - 1) // S
+    got = []
+    for spare, row in ((0, int(npg.max())), (3 * int(npg.sum()) + 40 * hkv + 4000, 4 * int(npg.max()) + 900)):
+        ids = rng.permutation(int(npg.sum()) + spare)[:int(npg.sum())]
+        bt = np.full((R, row), -1, np.int32)
+        dest = np.empty(T, np.int64)
+        for r in range(R):
+            mine = ids[npg[:r].sum():npg[:r + 1].sum()]
+            bt[r, :npg[r]] = mine
+            at = np.arange(P[r])
+            dest[kvo[r]:kvo[r + 1]] = mine[at // S] * S + at % S
+        pages = []
+        for c in (kc, vc):
+            t = torch.zeros(((len(ids) + spare) * S, hkv, 128), dtype=torch.int16, device="cuda:0")
+            t[_dev(dest)] = c
+            pages.append(t.view(-1, S, hkv, 128))
+        out, lse = new(nq, hq, 128), new(nq, hq)
+        status = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+        pkg.echo_tree_verify_attn_paged(q, kn, vn, *pages, S, _dev(bt), _dev(P.astype(np.int32)), qo,
+                                        mask, 1, R, nq, hq, hkv, 128, 0.088, out, lse, ws,
+                                        status=status)
+        assert int(status.item()) == 0
+        got.append((out.view(torch.int32), lse.view(torch.int32)))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    if same:
+        assert torch.equal(got[0][0], ref.view(torch.int32))
+        assert torch.equal(got[0][1], ref_lse.view(torch.int32))
+    else:
+        # two roundings of the weights to bf16: see compare_attn's bounds
+        scale = ref.abs().amax(-1, keepdim=True)
+        assert ((got[0][0].view(torch.float32) - ref).abs() <= 2 * gc.RTOL_ROW * scale).all()
+        assert (got[0][1].view(torch.float32) - ref_lse).abs().max() <= 2 * gc.LSE_ATOL
 
 
 def test_paged_attention_missing_page_skips_the_request():
