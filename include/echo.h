@@ -263,7 +263,8 @@ size_t echo_build_tree_mask_workspace_size(int32_t R, int32_t N, int32_t budget)
  * kv_rows and keeps the kernel for few rows there; otherwise the two calls
  * give the same bits.  max_rows and kv_rows best state the batch at hand (the
  * slots that exist, or R + budget) rather than what its arrays could hold: 32
- * requests of one slot under a max_rows of 1024 take 5% longer.
+ * requests of one slot under a max_rows of 1024 take 5% longer, 16 of four
+ * slots and 300 keys under 512 14%.
  */
 int32_t echo_tree_verify_attn(const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new,
                               const uint16_t* k_cache, const uint16_t* v_cache,

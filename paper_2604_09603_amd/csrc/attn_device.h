@@ -89,17 +89,26 @@ __host__ inline size_t unit_capacity(int R, int max_rows, int hq, int hkv) {
 // Whether a launch runs wide units: one KV head and up to 256 rows per unit,
 // its tiles copied once into an LDS ring that eight waves of 32 rows share.
 // Ordinary units copy a head's tiles once per pass of 64 rows, and with fewer KV
-// heads than their four waves also once per wave.  Measured on single calls (us,
-// ordinary -> wide; rows: per KV head, the mean of max_rows / R slots):
-// * 128 rows and more: 125.9 -> 117.7 (64 / 4 heads, 16 requests of 8000 keys),
-//   180.7 -> 164.9 (128 / 8, 4 of 20,000), 45.7 -> 41.2 (64 / 1, 32 of 1000);
-//   below it, with four heads or more, even (148.3 -> 148.8, 64 / 8, 104 rows) or
-//   slower (91.6 -> 95.0, 64 / 4, 80 rows), so there the ordinary ones are kept;
-// * fewer rows over fewer than four heads: 80.4 -> 62.0 (8 / 1, 128 of 4000: 62
-//   tiles per workgroup), but 26.3 -> 29.3 (8 / 1, 32 of 1000: 4 tiles), where
-//   the ring's start-up shows: wide from 32 tiles per workgroup on.  Two heads fill an
-//   ordinary unit with two passes each and stay even (111.4 -> 110.3, 16 / 2, 24 rows;
-//   152.2 -> 155.9, 64 / 2, 96 rows): not wide.
+// heads than their four waves also once per wave.  Measured on single calls over 1-512
+// requests of 33-32,000 keys, of equal size (us, ordinary -> wide; rows: per KV head, the
+// mean of max_rows / R slots):
+// * more than 128 rows: 117.2 -> 94.4 (64 / 4 heads, 12 slots, 32 requests of 4000 keys),
+//   27.9 -> 23.0 (64 / 1, 8 slots, 4 of 300), 53.3 -> 54.8 (64 / 8, 17 slots, 128 of 33).
+//   Of 824 shapes 24 lose more than 3%, all of them with at most 3000 keys, most by up to
+//   6%; the most where the ordinary units happen to be one per workgroup (25.2 -> 35.1,
+//   40 / 5, 17 slots, 64 of 33);
+// * 128 rows fill two ordinary passes: wide from 1024 keys per request on (58.9 -> 47.8,
+//   64 / 8, 32 of 1000; 79.7 -> 84.4, 64 / 4, 128 of 1000; 46.4 -> 49.1, 128 of 300), with
+//   two heads at any length (29.6 -> 22.1, 64 / 2, 128 of 33; 29.7 -> 31.4, 96 of 33);
+// * fewer rows over four heads or more: even (148.3 -> 148.8, 64 / 8, 104 rows) or slower
+//   (91.6 -> 95.0, 64 / 4, 80 rows); two heads: even (111.4 -> 110.3, 16 / 2, 24 rows;
+//   152.2 -> 155.9, 64 / 2, 96 rows): not wide;
+// * up to 128 rows over one head: 68.0 -> 55.1 (8 / 1, 128 of 4000: 62 tiles per
+//   workgroup), 45.0 -> 42.8 (64 rows, 128 of 2000: 31), but 21.7 -> 25.1 (16 / 1, 128 of
+//   200: 3), where the ring's start-up shows: from 32 tiles per workgroup on;
+// * over three heads: 73.7 -> 66.4 (24 rows, 64 of 3000: 70 tiles per workgroup), 65.1 ->
+//   64.3 (256 of 700: 66), 52.3 -> 55.0 (8 rows, 128 of 1300: 61), 47.0 -> 51.4 (24 rows,
+//   64 of 2000: 47): from 64 on.
 // kv_keys: the cached keys of all requests, as far as the host knows them (a contiguous
 // cache's kv_rows; of a paged cache only the pool's and the table's sizes are known, and
 // an engine's are many times its prefixes: 0, so that short prefixes in a large pool keep
@@ -107,15 +116,19 @@ __host__ inline size_t unit_capacity(int R, int max_rows, int hq, int hkv) {
 // the results don't follow the pool's size).  prefix_cap: the longest prefix there can be.
 // The 32-bit tile numbers must hold every request at that prefix whatever
 // the slots' spread; beyond that the ordinary units, with fewer tiles, are kept.
+constexpr int kWideKeys = 1024;
 __host__ inline bool attn_is_wide(int R, int max_rows, int hq, int hkv, long long prefix_cap,
                                   long long kv_keys, int nb) {
   if (R <= 0 || hkv <= 0) return false;
   const long long G = hq / hkv;
   const long long mean = (long long)(max_rows / R) * G;
   if (hkv >= 1 << 15) return false;  // (24-bit products in the copies' addresses)
-  if (mean < 2 * kPassRows &&
-      (hkv >= kWaves || hkv == 2 || kv_keys / kTileKeys * hkv < 32ll * nb))
-    return false;
+  bool wide = mean > 2 * kPassRows;
+  if (!wide && (hkv == 1 || hkv == 3))
+    wide = kv_keys / kTileKeys * hkv >= (hkv == 1 ? 32ll : 64ll) * nb;
+  else if (!wide)
+    wide = mean == 2 * kPassRows && (hkv == 2 || kv_keys >= (long long)kWideKeys * R);
+  if (!wide) return false;
   const long long passes = ((long long)max_rows * G + kWideRows - 1) / kWideRows + R;
   const long long tiles = prefix_cap / kTileKeys + max_rows / kTileKeys + 2;
   return tiles < (1ll << 29) / (passes * hkv);
