@@ -4,11 +4,10 @@
 //
 //   target_argmax   one workgroup per slot row: streams the row's bfloat16
 //                   logits with 16-byte loads, two batches in flight per thread
-//                   (HBM-bound: Nq * V * 2 bytes), as ordered 16-bit integers: the
-//                   maximum of eight at a time, and the first block of eight that
-//                   holds the thread's largest; a workgroup reduction picks the
-//                   row's block and its first largest element.  Then the acceptance
-//                   kernel.
+//                   (HBM-bound: Nq * V * 2 bytes), as 16-bit integers: a thread
+//                   keeps its largest value and the first group of blocks of eight
+//                   that holds it; the threads that have the row's largest then find
+//                   its first element.  Then the acceptance kernel.
 //   commit_kv       one workgroup per request: copies the root slot's and the
 //                   accepted slots' K and V rows into their pages, then advances
 //                   the request's cached length.
@@ -22,38 +21,56 @@ constexpr int kCommitThreads = 256;
 typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 typedef short short2v __attribute__((ext_vector_type(2)));
 
-// Two bfloat16 as signed 16-bit integers in their numeric order (-0 below +0;
-// negative NaN below -inf, positive NaN above +inf).
-__device__ __forceinline__ short2v ordered(uint32_t w) {
-  const short2v x = __builtin_bit_cast(short2v, w);
-  return x ^ ((x >> short2v{15, 15}) & short2v{0x7FFF, 0x7FFF});
-}
-constexpr int kOrdInf = 0x7F80;        // +inf
-constexpr int kOrdNegInf = -0x7F80 - 1;  // -inf
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
-// The row's argmax element by element, for the rows whose order as integers is not
-// the order asked for: NaN (never wins over a number), a maximum of zero (-0 and +0
-// are equal) or nothing above -inf (then the first -inf; only NaN: 0).  Every thread
-// of the workgroup calls it; the result is in s_best (value above, ~index below).
-template <int NT>
-__device__ __forceinline__ uint32_t argmax_plain(const uint16_t* row, long long vocab,
-                                                 unsigned long long* s_best) {
-  __syncthreads();
-  if (threadIdx.x == 0) *s_best = 0ull;
-  __syncthreads();
-  unsigned long long best = 0ull;
-  for (long long v = threadIdx.x; v < vocab; v += NT) {
-    const uint32_t u = uint32_t(row[v]);
-    if ((u & 0x7FFFu) > 0x7F80u) continue;  // NaN
-    const uint32_t b = u == 0x8000u ? 0u : u;  // -0 -> +0
-    const uint32_t k = (b & 0x8000u) ? (~b & 0xFFFFu) : (b | 0x8000u);
-    const unsigned long long w =
-        ((unsigned long long)(k + 1u) << 32) | (0xFFFFFFFFu - uint32_t(v));
-    best = w > best ? w : best;
+// Two bfloat16 as signed 16-bit integers in the order of the argmax: numbers as they
+// compare (-0 and +0 are both kOrdZero), NaN of either sign below -inf.  Two's
+// complement magnitudes, moved up by kOrdZero: the positive NaN, above +inf, wrap
+// around to the bottom, where the negative ones are.
+constexpr short kOrdZero = 0x7F;
+constexpr int kOrdNegInf = kOrdZero - 0x7F80;
+__device__ __forceinline__ short2v ordered(uint32_t w) {
+  const short2v neg = __builtin_bit_cast(short2v, w) >> short2v{15, 15};  // 0 or -1
+  const short2v mag = __builtin_bit_cast(short2v, w & 0x7FFF7FFFu);
+  return __builtin_bit_cast(  // (in unsigned arithmetic, which wraps)
+      short2v, __builtin_bit_cast(ushort2v, mag ^ neg) +
+                   __builtin_bit_cast(ushort2v, short2v{kOrdZero, kOrdZero} - neg));
+}
+
+// The largest of a block's eight elements, in that order.
+__device__ __forceinline__ int block_max(const uint4& x) {
+  const short2v m = __builtin_elementwise_max(
+      __builtin_elementwise_max(ordered(x.x), ordered(x.y)),
+      __builtin_elementwise_max(ordered(x.z), ordered(x.w)));
+  return max(int(m[0]), int(m[1]));
+}
+
+// The same over N blocks, with two instructions per two elements instead of five: the
+// largest bit pattern as signed (a positive one wins, in its order) and the smallest as
+// unsigned (without positive ones, the negative one nearest to zero).  A positive NaN
+// takes the plain order.
+template <int N>
+__device__ __forceinline__ int group_max(const uint4* x) {
+  short2v hi = __builtin_bit_cast(short2v, x[0].x);
+  ushort2v lo = __builtin_bit_cast(ushort2v, x[0].x);
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const uint32_t w[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      hi = __builtin_elementwise_max(hi, __builtin_bit_cast(short2v, w[k]));
+      lo = __builtin_elementwise_min(lo, __builtin_bit_cast(ushort2v, w[k]));
+    }
   }
-  if (best != 0ull) atomicMax(s_best, best);
-  __syncthreads();
-  return *s_best == 0ull ? 0u : 0xFFFFFFFFu - uint32_t(*s_best);
+  const int p = max(int(hi[0]), int(hi[1]));
+  const int n = min(int(lo[0]), int(lo[1]));
+  if (p > 0x7F80) {
+    int o = block_max(x[0]);
+#pragma unroll
+    for (int u = 1; u < N; ++u) o = max(o, block_max(x[u]));
+    return o;
+  }
+  return p >= 0 ? p + kOrdZero : kOrdZero - (n & 0x7FFF);
 }
 
 // One workgroup of NT threads per slot row, kArgBatch 16-byte loads per batch.
@@ -66,12 +83,19 @@ __device__ __forceinline__ uint32_t argmax_plain(const uint16_t* row, long long 
 //   end).  For the smaller case the hint is slower (12.0).
 // (Before: one batch of eight loads at a time, compared as floats element by
 // element, four instructions each, and a remainder of single loads.)
+// NaN and zeros of either sign cost nothing: rows that hold them once took a second,
+// element-by-element pass, and one such row 14.5 -> 64 us (160 x 151,936), 24 -> 79 (384).
+//
+// A thread keeps its largest value and the first group of kArgGroup blocks that holds
+// it; once the row's largest is known, those that have it look the element up.
+constexpr int kArgGroup = 5;
 template <int NT, int kArgBatch, bool kStream>
 __global__ __launch_bounds__(NT) void target_argmax_kernel(
     const uint16_t* __restrict__ logits, long long vocab, const int32_t* __restrict__ q_offsets,
     int R, int32_t* __restrict__ target) {
-  __shared__ unsigned long long s_wave[NT / kWave];
-  __shared__ unsigned long long s_best;
+  static_assert(kArgBatch % kArgGroup == 0, "whole groups");
+  __shared__ uint32_t s_wave[NT / kWave];
+  __shared__ uint32_t s_first;
   const int s = blockIdx.x;
   const uint16_t* row = logits + size_t(s) * size_t(vocab);
   const int tid = threadIdx.x;
@@ -83,7 +107,8 @@ __global__ __launch_bounds__(NT) void target_argmax_kernel(
   const uint4* body = reinterpret_cast<const uint4*>(row + head);
   if (s >= q_offsets[R]) return;  // uniform over the workgroup
   int best = -0x8000 - 1;  // below every ordered value
-  uint32_t at = 0u;        // its element (head, tail) or the first one of its block
+  uint32_t at = 0u;        // its element (head, tail) or its group's first block
+  bool group = false;
   // the head precedes the blocks in index order: taken first
   for (long long v = tid; v < head; v += NT) {
     const int o = int(ordered(row[v])[0]);
@@ -109,15 +134,12 @@ __global__ __launch_bounds__(NT) void target_argmax_kernel(
     };
     const auto take = [&](const uint4 (&x)[kArgBatch], long long c) {
 #pragma unroll
-      for (int u = 0; u < kArgBatch; ++u) {
-        const long long i = c + (long long)u * NT;
-        const short2v m = __builtin_elementwise_max(
-            __builtin_elementwise_max(ordered(x[u].x), ordered(x[u].y)),
-            __builtin_elementwise_max(ordered(x[u].z), ordered(x[u].w)));
-        const int o = max(int(m[0]), int(m[1]));
+      for (int g = 0; g < kArgBatch; g += kArgGroup) {
+        const int o = group_max<kArgGroup>(&x[g]);
         if (o > best) {
           best = o;
-          at = uint32_t(head + (i < nvec ? i : nvec - 1) * 8);
+          at = uint32_t(c + (long long)g * NT);
+          group = true;
         }
       }
     };
@@ -136,35 +158,52 @@ __global__ __launch_bounds__(NT) void target_argmax_kernel(
     if (o > best) {
       best = o;
       at = uint32_t(v);
+      group = false;
     }
   }
-  // largest value, then the smallest place
-  unsigned long long w =
-      ((unsigned long long)(uint32_t(best + 0x8001)) << 32) | (0xFFFFFFFFu - at);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const unsigned long long o = __shfl_xor(w, off, kWave);
-    w = o > w ? o : w;
-  }
-  if ((tid & (kWave - 1)) == 0) s_wave[tid / kWave] = w;
+  const uint32_t wmax = wave_max(uint32_t(best + 0x8001));
+  if ((tid & (kWave - 1)) == 0) s_wave[tid / kWave] = wmax;
+  if (tid == 0) s_first = 0xFFFFFFFFu;
   __syncthreads();
+  uint32_t w = s_wave[0];
 #pragma unroll
-  for (int k = 0; k < NT / kWave; ++k) w = s_wave[k] > w ? s_wave[k] : w;
-  const int top = int(uint32_t(w >> 32)) - 0x8001;
-  uint32_t idx = 0xFFFFFFFFu - uint32_t(w);
-  if (top > kOrdInf || top == 0 || top <= kOrdNegInf) {  // uniform, rare
-    idx = argmax_plain<NT>(row, vocab, &s_best);
-  } else if (idx >= head && (long long)idx < tail0) {
-    // the first of the block's eight elements with that value
-    const uint4 x = *reinterpret_cast<const uint4*>(row + idx);
-    const short2v o[4] = {ordered(x.x), ordered(x.y), ordered(x.z), ordered(x.w)};
-    uint32_t e = 7u;
+  for (int k = 1; k < NT / kWave; ++k) w = max(w, s_wave[k]);
+  const int top = int(w) - 0x8001;
+  uint32_t idx = 0xFFFFFFFFu;
+  if (best == top) {
+    idx = at;
+    if (group) {
+      // the group's first block with that value, then its first element
+      uint4 x[kArgGroup];
+      uint32_t blk[kArgGroup];
 #pragma unroll
-    for (int k = 6; k >= 0; --k)
-      if (int(o[k >> 1][k & 1]) == top) e = uint32_t(k);
-    idx += e;
+      for (int u = 0; u < kArgGroup; ++u) {
+        const long long i = (long long)at + (long long)u * NT;
+        blk[u] = uint32_t(i < nvec ? i : nvec - 1);
+        x[u] = body[blk[u]];
+      }
+      uint4 y = x[kArgGroup - 1];
+      uint32_t in = blk[kArgGroup - 1];
+#pragma unroll
+      for (int u = kArgGroup - 2; u >= 0; --u) {
+        if (block_max(x[u]) == top) {
+          y = x[u];
+          in = blk[u];
+        }
+      }
+      const short2v o[4] = {ordered(y.x), ordered(y.y), ordered(y.z), ordered(y.w)};
+      uint32_t e = 7u;
+#pragma unroll
+      for (int k = 6; k >= 0; --k)
+        if (int(o[k >> 1][k & 1]) == top) e = uint32_t(k);
+      idx = uint32_t(head) + in * 8u + e;
+    }
   }
-  if (tid == 0) target[s] = int32_t(idx);
+  // (one atomic per wave: in a row of equal logits every thread is here)
+  const uint32_t first = ~wave_max(~idx);
+  if ((tid & (kWave - 1)) == 0 && first != 0xFFFFFFFFu) atomicMin(&s_first, first);
+  __syncthreads();
+  if (tid == 0) target[s] = top < kOrdNegInf ? 0 : int32_t(s_first);  // (only NaN: 0)
 }
 
 __global__ __launch_bounds__(kCommitThreads) void commit_kv_kernel(

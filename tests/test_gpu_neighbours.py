@@ -84,3 +84,29 @@ def test_attention_kernel_of_short_prefixes(R, slots, keys, hq, hkv):
     assert _ratio(f"{hq}/{hkv} heads, {R} x {slots} slots, {keys} keys",
                   _attention(R, slots, keys, hq, hkv),
                   _attention(R, slots, keys, hq, hkv, spare=400000)) < 0.92
+
+
+def _argmax(rows, vocab, spoil=None):
+    """A call of the target argmax over `rows` rows of logits; spoil: what one row holds."""
+    import torch
+    import paper_2604_09603_amd as pkg
+    x = torch.randn(rows, vocab, device="cuda:0", dtype=torch.bfloat16)
+    x[:, vocab // 3] = 9.0
+    if spoil == "NaN":
+        x[rows // 2, 7] = float("nan")
+    elif spoil == "zero":
+        x[rows // 2] = -x[rows // 2].abs()
+        x[rows // 2, 7] = 0.0
+    qo, parent = _dev(np.arange(rows + 1, dtype=np.int32)), _dev(np.full(rows, -1, np.int32))
+    tok, tgt, al, sl, bonus = _i32(rows), _i32(rows), _i32(rows), _i32(rows, 16), _i32(rows)
+    x = x.view(torch.int16)
+    return lambda: pkg.echo_accept_logits(qo, parent, tok, x, rows, rows, 16, tgt, al, sl, bonus)
+
+
+@pytest.mark.parametrize("spoil", ["NaN", "zero"])
+@pytest.mark.parametrize("rows", [160, 384])
+def test_argmax_unusual_row(rows, spoil):
+    """One row with a NaN, or with a largest logit of zero, does not set the time of the
+    batch: 1.0; 3.3 to 4.4 with a second pass over such a row."""
+    assert _ratio(f"argmax, one {spoil} row of {rows}", _argmax(rows, 151936, spoil),
+                  _argmax(rows, 151936)) < 1.5
