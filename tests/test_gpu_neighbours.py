@@ -110,3 +110,11 @@ def test_argmax_unusual_row(rows, spoil):
     batch: 1.0; 3.3 to 4.4 with a second pass over such a row."""
     assert _ratio(f"argmax, one {spoil} row of {rows}", _argmax(rows, 151936, spoil),
                   _argmax(rows, 151936)) < 1.5
+
+
+@pytest.mark.parametrize("rows,bound", [(160, 0.87), (384, 0.68)])
+def test_argmax_short_rows(rows, bound):
+    """A row of 1000 logits takes less than one of 64 times as many: 0.74 and 0.51; 1.00
+    and 0.83 where a row always runs three batches of loads."""
+    assert _ratio(f"argmax, {rows} rows of 1000 and of 64,000", _argmax(rows, 1000),
+                  _argmax(rows, 64000)) < bound

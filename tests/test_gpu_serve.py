@@ -329,6 +329,34 @@ def test_target_argmax_edges(vocab, rows):
     assert np.array_equal(target.cpu().numpy(), want["target_token"])
 
 
+@pytest.mark.parametrize("vocab", [9, 1000, 8200, 40959, 40969, 90001])
+@pytest.mark.parametrize("rows", [7, 300])
+def test_target_argmax_negative_rows(vocab, rows):
+    """Rows without a positive logit, whose order is by the bit patterns' other end: ties,
+    NaN of both signs among them, a largest logit of -0 alone, -inf beside NaN; and a
+    maximum in the last block and in the last element.  Against the oracle, exactly."""
+    import torch
+    import paper_2604_09603_amd as pkg
+    rng = np.random.default_rng(vocab + 3 * rows)
+    vals = -(rng.integers(1, 200, (rows, vocab)).astype(np.float32)) / 4
+    bits = synth.f32_to_bf16_bits(vals).reshape(rows, vocab).copy()
+    bits[1] = np.where(rng.random(vocab) < 0.2, 0x7FC0, np.where(rng.random(vocab) < 0.2, 0xFFC0, bits[1]))
+    bits[2, rng.integers(0, vocab, 3)] = 0x8000
+    bits[3] = np.where(rng.random(vocab) < 0.5, 0xFF80, np.where(rng.random(vocab) < 0.5, 0xFFFF, 0x7F81))
+    bits[4, vocab - 1] = 0x0001
+    bits[5, (vocab - 1) // 8 * 8 - (8 if vocab > 8 else 0)] = 0x3F80
+    bits[6] = 0x7F80 if vocab == 9 else 0x8000
+    i32 = lambda *s: torch.zeros(s, dtype=torch.int32, device="cuda:0")
+    target = i32(rows)
+    qo, par = np.arange(rows + 1, dtype=np.int32), np.full(rows, -1, np.int32)
+    _log(f"[serve] argmax of negative logits V={vocab} rows={rows}")
+    pkg.echo_accept_logits(_dev(qo), _dev(par), i32(rows), _dev(bits.view(np.int16)), rows, rows,
+                           16, target, i32(rows), i32(rows, 16), i32(rows))
+    torch.cuda.synchronize()
+    want = oracle.accept_from_logits(qo, par, np.zeros(rows, np.int32), bits, 16)
+    assert np.array_equal(target.cpu().numpy(), want["target_token"])
+
+
 def test_commit_kv_matches_oracle():
     import torch
     import paper_2604_09603_amd as pkg
