@@ -30,6 +30,10 @@ struct GateScoreBufs {
   const int32_t* pglob;
   const uint8_t* depth;
 };
+// Writes them (and path_score) in a launch of its own.
+int32_t launch_gate_score(const int32_t* cand_offsets, const int32_t* parent, const float* logq,
+                          int32_t R, int32_t N, float* path_score, void* workspace,
+                          int32_t* status, hipStream_t stream);
 
 // Alg. 1 scheduler (checkpoint table as for launch_gate; w_topk >= 1, w_max >= 0).
 int32_t launch_gate_elastic(const int32_t* cand_offsets, const int32_t* parent, const float* logq,

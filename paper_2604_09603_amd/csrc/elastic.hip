@@ -6,10 +6,13 @@
 // or fails and is truncated.  Phase 2 widens every truncated request's last
 // kept depth up to W_max nodes while budget is left.
 //
-// Two launches (three beyond kFinThreads requests).  The coupling between requests
-// is only through the budget, and until the budget runs out every request receives
-// its whole demand, so each request's phase-1 trajectory can be computed on its own:
+// Two launches, three with many or large requests (see elastic_scores_in_request) and
+// one more beyond kFinThreads requests.  The coupling between requests is only through
+// the budget, and until the budget runs out every request receives its whole demand, so
+// each request's phase-1 trajectory can be computed on its own:
 //
+//   gate_score        (shared with the top-B gate; many or large requests) the path
+//                     scores, one thread per candidate
 //   elastic_request   one workgroup per request: its candidates' path scores, then
 //                     its full-grant trajectory -- per depth the appendable
 //                     candidates (parent held), the checkpoint test, the demand
@@ -224,7 +227,8 @@ __device__ int staged_scores(int lo, int n, const ElasticPool& ep, ElasticLds& L
   constexpr uint32_t kUnknown = 0x7FFFFFFFu;  // a NaN: no clamped score is one
   // kPer candidates per thread in registers: a round is one LDS round trip (read
   // from LDS one after another, three each, the rounds took 4 us).  Requests with
-  // more take several passes; a candidate's parent is never in a later one.
+  // more take several passes; a candidate's parent is never in a later one.  (16 per
+  // thread and one pass: 21.8 -> 26.7 us at 1 x 1100 candidates, the code is longer.)
   constexpr int kPer = 4;
   const int tid = threadIdx.x;
   int bits = 0;
@@ -291,23 +295,113 @@ __device__ int staged_scores(int lo, int n, const ElasticPool& ep, ElasticLds& L
   return bits;
 }
 
-// The same for a request too large for LDS: each candidate walks its path in memory.
+// The same for a request too large for LDS: each candidate walks its path in memory
+// (as node_score), kWalk of them at once per thread: a level is one round trip.  127
+// requests of 700 and one of 4200: 78.5 -> 71.0 us (66.8 with scores of their own launch;
+// eight at once 72.6, with the path in LDS and short code 76.5).
 __device__ int global_scores(int lo, int n, const ElasticPool& ep) {
+  constexpr int kWalk = 4;
   int bits = 0;
-  for (int g = lo + int(threadIdx.x); g < lo + n; g += kElThreads) {
-    const NodeScore ns = node_score(g, lo, [&](int x) { return ep.parent[x]; },
-                                    [&](int x) { return ep.logq[x]; });
-    bits |= ns.bits;
-    ep.keys[g] = ns.key;
-    ep.pglob[g] = ns.parent;
-    ep.depth[g] = uint8_t(min(ns.depth, ECHO_MAX_DEPTH + 1));
-    if (ep.path_score != nullptr) ep.path_score[g] = ns.score;
+  for (int i0 = threadIdx.x; i0 < n; i0 += kWalk * kElThreads) {
+    int own[kWalk], p[kWalk], depth[kWalk];
+    float vals[kWalk][ECHO_MAX_DEPTH + 1];
+#pragma unroll
+    for (int q = 0; q < kWalk; ++q) {
+      const int i = min(i0 + q * kElThreads, n - 1);
+      own[q] = ep.parent[lo + i];
+      vals[q][0] = ep.logq[lo + i];
+    }
+#pragma unroll
+    for (int q = 0; q < kWalk; ++q) {
+      const int i = i0 + q * kElThreads;
+      depth[q] = 1;
+      if (own[q] < -1 || own[q] >= min(i, n - 1)) {
+        if (i < n) bits |= ECHO_DATA_BAD_PARENT;
+        own[q] = -1;
+      }
+      float& v = vals[q][0];
+      if (v != v) {
+        if (i < n) bits |= ECHO_DATA_NAN_LOGQ;
+        v = -__builtin_inff();
+      } else if (v > 0.0f) {
+        if (i < n) bits |= ECHO_DATA_POS_LOGQ;
+        v = 0.0f;
+      }
+      p[q] = own[q];
+    }
+#pragma unroll
+    for (int l = 1; l <= ECHO_MAX_DEPTH; ++l) {
+      bool on = false;
+#pragma unroll
+      for (int q = 0; q < kWalk; ++q) {
+        vals[q][l] = 0.0f;
+        on = on || p[q] >= 0;
+      }
+      if (__ballot(on) == 0ull) continue;
+      float v[kWalk];
+      int pp[kWalk];
+#pragma unroll
+      for (int q = 0; q < kWalk; ++q) {
+        v[q] = ep.logq[lo + max(p[q], 0)];
+        pp[q] = ep.parent[lo + max(p[q], 0)];
+      }
+#pragma unroll
+      for (int q = 0; q < kWalk; ++q) {
+        if (p[q] < 0) continue;
+        vals[q][l] = v[q] != v[q] ? -__builtin_inff() : fminf(v[q], 0.0f);
+        depth[q] = l + 1;
+        p[q] = pp[q] < -1 || pp[q] >= p[q] ? -1 : pp[q];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kWalk; ++q) {
+      const int i = i0 + q * kElThreads;
+      if (i >= n) continue;
+      float s = -__builtin_inff();
+      if (depth[q] > ECHO_MAX_DEPTH) {
+        bits |= ECHO_DATA_TOO_DEEP;
+      } else {
+        s = 0.0f;
+#pragma unroll
+        for (int l = ECHO_MAX_DEPTH; l >= 0; --l)
+          if (l < depth[q]) s = s + vals[q][l];
+      }
+      ep.keys[lo + i] = score_key(s);
+      ep.pglob[lo + i] = own[q] < 0 ? -1 : lo + own[q];
+      ep.depth[lo + i] = uint8_t(depth[q]);
+      if (ep.path_score != nullptr) ep.path_score[lo + i] = s;
+    }
   }
   return bits;
 }
 
-// Trajectory of a request whose candidates fit in LDS (staged_scores left them
-// there): they are grouped by depth once, so each depth visits only its own
+// Scores that gate_score has left in the workspace, of a request whose candidates fit
+// in LDS: all of a thread's candidates are fetched before any is stored.
+__device__ void staged_load(int lo, int n, const GateScoreBufs& sb, ElasticLds& L) {
+  constexpr int kPer = kElCap / kElThreads;
+  const int tid = threadIdx.x;
+  uint32_t kk[kPer];
+  int pp[kPer], dd[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int i = tid + q * kElThreads;
+    kk[q] = i < n ? sb.keys[lo + i] : 0u;
+    pp[q] = i < n ? sb.pglob[lo + i] : -1;
+    dd[q] = i < n ? int(sb.depth[lo + i]) : 0;
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int i = tid + q * kElThreads;
+    if (i < n) {
+      L.key[i] = kk[q];
+      L.par[i] = pp[q] < 0 ? -1 : pp[q] - lo;
+      L.dep[i] = uint8_t(dd[q]);
+    }
+  }
+}
+
+// Trajectory of a request whose candidates fit in LDS (staged_scores or staged_load
+// left them there): they are grouped by depth once, so each depth visits only its own
 // candidates.
 __device__ void trajectory_staged(int r, int lo, int n, const ElasticArgs& ea, const ElasticWs& ew,
                                   ElasticLds& L) {
@@ -430,12 +524,28 @@ __device__ void trajectory_global(int r, int lo, int n, const GateScoreBufs& sb,
   if (tid == 0) write_trajectory(r, t, ea, ew, L);
 }
 
+// kScored: gate_score has run (keys, parents and depths are in the pool's outputs).
+template <bool kScored>
 __global__ __launch_bounds__(kElThreads) void elastic_request_kernel(
     const int32_t* __restrict__ cand_offsets, int R, int N, ElasticPool ep, ElasticArgs ea,
     ElasticWs ew, int32_t* status) {
   __shared__ ElasticLds L;
   const int r = blockIdx.x;
   int lo = cand_offsets[r], hi = cand_offsets[r + 1];
+  const GateScoreBufs sb{ep.keys, ep.pglob, ep.depth};
+  if (kScored) {
+    // a malformed CSR has left every key at 0 (nothing appendable); only keep the
+    // range in bounds
+    if (lo < 0 || hi > N || hi < lo) lo = hi = 0;
+    if (hi - lo <= kElCap) {
+      staged_load(lo, hi - lo, sb, L);
+      __syncthreads();
+      trajectory_staged(r, lo, hi - lo, ea, ew, L);
+    } else {
+      trajectory_global(r, lo, hi - lo, sb, ea, ew, L);
+    }
+    return;
+  }
   // the candidate CSR must be well formed before anything is read through it; a
   // malformed one leaves every key at 0 (nothing appendable)
   bool bad = false;
@@ -463,7 +573,7 @@ __global__ __launch_bounds__(kElThreads) void elastic_request_kernel(
   } else {
     bits |= global_scores(lo, n, ep);
     __syncthreads();
-    trajectory_global(r, lo, n, GateScoreBufs{ep.keys, ep.pglob, ep.depth}, ea, ew, L);
+    trajectory_global(r, lo, n, sb, ea, ew, L);
   }
   wave_status_or(status, bits);
 }
@@ -634,7 +744,7 @@ __device__ __forceinline__ int own_grants(int R, int budget, const ElasticWs& ew
   return cut;
 }
 
-// kOwn: R <= kSelThreads, the grants are found here; else elastic_finish has.
+// kOwn (R <= kSelThreads): the grants are found here; else elastic_finish has.
 template <bool kOwn>
 __global__ __launch_bounds__(kSelThreads) void elastic_select_kernel(
     const int32_t* __restrict__ cand_offsets, int R, int N, int budget, GateScoreBufs sb,
@@ -678,6 +788,17 @@ __global__ __launch_bounds__(kSelThreads) void elastic_select_kernel(
 
 }  // namespace
 
+// Whether the request launch finds the path scores itself, or a launch before it (one
+// thread per candidate) does.  The first saves a launch and its trips through memory
+// (27.0 -> 24.5 us, 128 requests of 710; 23.6 -> 20.8, 256 of 300), as long as every
+// request's workgroup has a CU to itself (its LDS leaves room for no second one, and each
+// round of them pays for the scores again: 28.7 -> 29.7, 300 of 300; 46.3 -> 57.3, 1024 of
+// 88; 151 -> 248, 4000 of 20) and a request's candidates are one pass (26.0 -> 23.9, 32 of
+// 1024; 21.8 -> 22.8, 1 of 1100; 59.1 -> 63.2, 1 of 4096).  The host knows their mean.
+static bool elastic_scores_in_request(int32_t R, int32_t N) {
+  return R <= device_cu_count() && N <= 1024ll * R;
+}
+
 size_t gate_elastic_workspace_bytes(int32_t R, int32_t N, int32_t budget) {
   return el_align(gate_workspace_bytes(R, N, budget)) + elastic_own_bytes(R, N);
 }
@@ -705,13 +826,17 @@ int32_t launch_gate_elastic(const int32_t* cand_offsets, const int32_t* parent, 
   const GateScoreBufs sb{gws.keys, gws.pglob, gws.depth};
   char* own = static_cast<char*>(workspace) + el_align(gate_workspace_bytes(R, N, budget));
   const ElasticWs ew = elastic_ws_layout(own, R, N);
-  hipLaunchKernelGGL(elastic_request_kernel, dim3(R), dim3(kElThreads), 0, stream, cand_offsets, R,
-                     N, ep, ea, ew, status);
+  const bool scored = !elastic_scores_in_request(R, N);
+  if (scored && launch_gate_score(cand_offsets, parent, logq, R, N, path_score, workspace, status,
+                                  stream) != ECHO_OK)
+    return ECHO_ERR_HIP;
+  hipLaunchKernelGGL(scored ? elastic_request_kernel<true> : elastic_request_kernel<false>, dim3(R),
+                     dim3(kElThreads), 0, stream, cand_offsets, R, N, ep, ea, ew, status);
+  const int blocks = (N + kSelThreads - 1) / kSelThreads;
   const bool own_grants_fit = R <= kSelThreads;
   if (!own_grants_fit)
     hipLaunchKernelGGL(elastic_finish_kernel, dim3(1), dim3(kFinThreads), 0, stream, R, budget, ew,
                        num_selected, trunc_depth);
-  const int blocks = (N + kSelThreads - 1) / kSelThreads;
   if (blocks > 0 || own_grants_fit)  // (without candidates: the grants' outputs only)
     hipLaunchKernelGGL(own_grants_fit ? elastic_select_kernel<true> : elastic_select_kernel<false>,
                        dim3(blocks > 0 ? blocks : 1), dim3(kSelThreads),

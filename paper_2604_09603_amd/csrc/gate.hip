@@ -503,6 +503,21 @@ int32_t launch_gate_select_only(const int32_t* cand_offsets, const int32_t* pare
                           list, stream);
 }
 
+int32_t launch_gate_score(const int32_t* cand_offsets, const int32_t* parent, const float* logq,
+                          int32_t R, int32_t N, float* path_score, void* workspace,
+                          int32_t* status, hipStream_t stream) {
+  const GateWs ws = gate_ws_layout(workspace, N, R);
+  SparseArgs sp{};
+  sp.enabled = 1;  // depths written, no histograms, no checkpoint maxima (mask 0)
+  sp.mask = 0u;
+  for (int d = 0; d < kDepths; ++d) sp.lt[d] = -__builtin_inff();
+  sp.trunc_out = nullptr;
+  hipLaunchKernelGGL(gate_score_kernel, dim3(gate_blocks(N)), dim3(kGateThreads),
+                     size_t(R + 1) * sizeof(int32_t), stream, cand_offsets, parent, logq, R, N, ws,
+                     path_score, status, sp);
+  return hipGetLastError() == hipSuccess ? ECHO_OK : ECHO_ERR_HIP;
+}
+
 size_t gate_workspace_bytes(int32_t R, int32_t N, int32_t budget) {
   (void)budget;
   return gate_ws_bytes(N, R);

@@ -167,12 +167,13 @@ def test_full_step_with_elastic_gate():
     gc.compare_attn(res["out"], res["lse"], ro, rl, range(m["num_slots"]))
 
 
-@pytest.mark.parametrize("R", [1, 1024, 1025])
+@pytest.mark.parametrize("R", [1, 6, 40, 1024, 1025])
 def test_request_and_grant_edges(R):
     """Requests on both sides of what one pass of the scores takes (1024
     candidates) and of what LDS takes (4096), with chains deeper than the depth
     limit across them, and request counts on both sides of what the select
-    launch grants by itself (1024)."""
+    launch grants by itself (1024).  The request launch finds the scores of 1 and 40
+    requests itself; 6 are too large on the mean, 1024 more than there are CUs."""
     rng = np.random.default_rng(R)
     sizes = np.full(R, 2)
     big = [1023, 1024, 1025, 3000, 4096, 4097][:R]

@@ -118,3 +118,35 @@ def test_argmax_short_rows(rows, bound):
     and 0.83 where a row always runs three batches of loads."""
     assert _ratio(f"argmax, {rows} rows of 1000 and of 64,000", _argmax(rows, 1000),
                   _argmax(rows, 64000)) < bound
+
+
+def _elastic(sizes):
+    """A call of the elastic scheduler over requests of these pool sizes (eight levels)."""
+    import torch
+    import paper_2604_09603_amd as pkg
+    from paper_2604_09603_amd.step import _aligned_workspace
+    rng = np.random.default_rng(len(sizes))
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    R, N = len(sizes), int(offs[-1])
+    parent = []
+    for n in sizes:
+        lev, i = n // 8 + 1, np.arange(n)
+        p = np.where(i < lev, -1, (i // lev - 1) * lev + (i % lev) // 8)
+        parent.append(np.minimum(p, i - 1))
+    offs, parent = _dev(offs), _dev(np.concatenate(parent).astype(np.int32))
+    logq = _dev(-rng.exponential(1.0, N).astype(np.float32))
+    score, num = torch.zeros(N, device="cuda:0"), _i32(1)
+    sel = torch.zeros(N, dtype=torch.uint8, device="cuda:0")
+    ws = _aligned_workspace(pkg.gate_elastic_workspace_size(R, N, 256), "cuda:0")
+    return lambda: pkg.echo_gate_elastic(offs, parent, logq, R, N, 256, [1, 3, 5],
+                                         [-3.0, -6.0, -9.0], 2, 10, score, sel, num, ws)
+
+
+@pytest.mark.parametrize("sizes,other,bound", [
+    ([88] * 1024, [710] * 128, 2.28), ([20] * 4000, [710] * 128, 8.8),
+    ([4200], [1000], 3.26)])
+def test_elastic_many_or_large_requests(sizes, other, bound):
+    """More requests than CUs and a request too large for LDS, against ordinary sizes:
+    2.0, 6.5 and 2.9; 2.6, 11.1 and 3.7 where every request's workgroup finds its scores."""
+    assert _ratio(f"elastic, {len(sizes)} x {sizes[0]} and {len(other)} x {other[0]}",
+                  _elastic(sizes), _elastic(other)) < bound
