@@ -193,3 +193,19 @@ def test_request_and_grant_edges(R):
     got = run_elastic_offsets(bad, parent.astype(np.int32), logq, N)
     assert got["status"] & 128 and got["num_selected"] == 0 and not got["selected"].any()
     assert np.all(np.isneginf(got["path_score"]))
+
+
+def test_more_select_workgroups_than_cus():
+    """As many candidates as take more select workgroups than the GPU has CUs: the grants
+    have a launch of their own."""
+    import torch
+    R = 1000
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 1024 // R + 2
+    rng = np.random.default_rng(2)
+    offs = (np.arange(R + 1) * n).astype(np.int32)
+    local = np.tile(np.arange(n), R)
+    parent = np.where(local % 3 == 0, -1, local // 20 - 1).astype(np.int32)
+    logq = rng.choice(np.array([0.0, -0.25, -0.5, -1.0], np.float32), R * n)
+    for budget, wt, wm in [(700, 2, 5), (9000, 4, 40)]:
+        _log(f"[elastic] N={R * n} B={budget}")
+        check(offs, parent, logq, budget, [2, 4], [-0.9, -1.6], wt, wm)

@@ -144,9 +144,11 @@ def _elastic(sizes):
 
 @pytest.mark.parametrize("sizes,other,bound", [
     ([88] * 1024, [710] * 128, 2.28), ([20] * 4000, [710] * 128, 8.8),
-    ([4200], [1000], 3.26)])
+    ([4200], [1000], 3.26), ([1000] * 1024, [710] * 128, 3.7)])
 def test_elastic_many_or_large_requests(sizes, other, bound):
-    """More requests than CUs and a request too large for LDS, against ordinary sizes:
-    2.0, 6.5 and 2.9; 2.6, 11.1 and 3.7 where every request's workgroup finds its scores."""
+    """More requests than CUs, a request too large for LDS and more candidates than one
+    workgroup per CU takes, against ordinary sizes: 2.0, 6.5, 2.9 and 3.3; 2.6, 11.1, 3.7
+    and 4.1 where every request's workgroup finds its scores and every select workgroup
+    the grants."""
     assert _ratio(f"elastic, {len(sizes)} x {sizes[0]} and {len(other)} x {other[0]}",
                   _elastic(sizes), _elastic(other)) < bound
