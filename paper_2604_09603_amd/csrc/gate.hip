@@ -405,11 +405,14 @@ __global__ __launch_bounds__(kGateThreads) void gate_finish_kernel(int N, int nb
 }
 
 // The whole gate of a small pool in one launch of one workgroup.  The three launches
-// are chains of round trips whatever N is, this one's search grows with N.  Three
-// launches -> one: 9.2 -> 5.2 us at 208 candidates, 10.9 -> 7.8 at 1280, 11.5 -> 9.4 at
-// 2560 (32 requests), 12.0 -> 10.3 at 2400 (16 requests); beyond kSmallPool candidates a
-// thread would hold a fourth one, and the two meet.
-static_assert((2 * kSmallPool + ECHO_MAX_REQUESTS + 1) * 4 <= 48 * 1024, "LDS of gate_small");
+// are chains of round trips whatever N is, this one's search grows with N and its scores
+// with the depth.  Three launches -> one: 9.6 -> 5.0 us at 208 candidates, 11.3 -> 7.8 at
+// 1280, 11.5 -> 10.0 at 2560; with chains of 16 levels 11.7 -> 7.6 at 200, 14.2 -> 13.9 at
+// 2048, 13.4 -> 13.9 at 2400.  At 3072 the trees gain (12.3 -> 10.6) and such chains and
+// equal scores lose (13.1 -> 15.3; 11.5 -> 12.2): hence the line.
+constexpr int kGatePool = 2560;
+static_assert(kGatePool <= kSmallPool, "candidates per thread");
+static_assert((2 * kGatePool + ECHO_MAX_REQUESTS + 1) * 4 <= 48 * 1024, "LDS of gate_small");
 __global__ __launch_bounds__(kGateThreads) void gate_small_kernel(
     const int32_t* __restrict__ cand_offsets, SmallGate a, int32_t* status) {
   extern __shared__ __attribute__((aligned(16))) int32_t smem[];  // 2 N words, R + 1 offsets
@@ -456,7 +459,7 @@ int32_t launch_gate_impl(const int32_t* cand_offsets, const int32_t* parent, con
     sp.mask |= 1u << d;
   }
   sp.trunc_out = trunc_depth;
-  if (!sp.enabled && finish && N <= kSmallPool) {
+  if (!sp.enabled && finish && N <= kGatePool) {
     const SmallGate a{N, R, budget, parent, logq, path_score, selected, num_selected};
     hipLaunchKernelGGL(gate_small_kernel, dim3(1), dim3(kGateThreads),
                        (size_t(2) * N + R + 1) * sizeof(int32_t), stream, cand_offsets, a, status);

@@ -398,7 +398,9 @@ __device__ void gate_finish_body(int N, int nblocks, const GateWs& ws,
 // workgroup, in LDS.  Whole fused steps over N candidates
 // (8 / 8 heads, 64 keys), lists -> small pool: 28.5 -> 23.3 us at 208, 32.1 -> 28.6
 // at 2080, 36.6 -> 34.7 at 3120, 38.7 -> 38.4 at 4160, 42.0 -> 44.7 at 6136 (one
-// workgroup's searches and histogram rounds grow with N).
+// workgroup's searches and histogram rounds grow with N).  A round of the scores was two
+// barriers then; with one, steps over 208, 2400 and 3072 candidates take 23.4 -> 22.1,
+// 34.5 -> 31.2 and 38.8 -> 35.2 us, the last two with chains of 16 levels.
 constexpr int kSmallPer = 3;
 constexpr int kSmallPool = kSmallPer * kGateThreads;
 
@@ -439,7 +441,9 @@ __device__ __forceinline__ auto select_small(const SmallGate& a, const SmallPool
                                              int32_t* smem, int* bits, Finish finish) {
   __shared__ RadixLds s_rl;
   __shared__ uint32_t s_fin[kGateThreads / kWave];
+  __shared__ uint32_t s_more[3];  // round r, entry r % 3: a node is still open
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  if (tid < 3) s_more[tid] = 0u;
   // Scores top-down, all nodes of a depth in one round: (score, depth) of every node
   // whose score is known, a NaN score where it is not.  A node folds the same
   // binary32 adds in the same order as a walk from the root.  (Short code: with the
@@ -475,8 +479,20 @@ __device__ __forceinline__ auto select_small(const SmallGate& a, const SmallPool
   }
   for (int i = tid; i < 512; i += kGateThreads) (&s_rl.h[0][0])[i] = 0u;
   // after ECHO_MAX_DEPTH - 1 rounds every node of depth <= ECHO_MAX_DEPTH is known
+  // (one barrier per round: a round's entry is cleared two rounds before it is set again,
+  // when everyone has read it)
+  int now = 0;
   for (int round = 1; round < ECHO_MAX_DEPTH; ++round) {
-    if (!__syncthreads_or(open != 0u)) break;
+    if (round == 1) {
+      if (!__syncthreads_or(open != 0u)) break;
+    } else {
+      if (__ballot(open != 0u) != 0ull && lane == 0) s_more[now] = 1u;
+      __syncthreads();
+      if (s_more[now] == 0u) break;
+      const int last = now == 0 ? 2 : now - 1;
+      if (tid == 0) s_more[last] = 0u;
+      now = now == 2 ? 0 : now + 1;
+    }
 #pragma unroll
     for (int k = 0; k < kSmallPer; ++k) {
       if (!((open >> k) & 1u)) continue;

@@ -140,10 +140,12 @@ def test_all_equal_scores_large_tie_class():
 
 
 @pytest.mark.parametrize("n,R,budget", [(0, 3, 4), (1, 1, 1), (1025, 9, 64), (3071, 40, 300),
-                                        (3072, 1, 3072), (3073, 40, 300), (3000, 4095, 200)])
+                                        (3072, 1, 3072), (3073, 40, 300), (3000, 4095, 200),
+                                        (2560, 1, 2560), (2560, 4095, 200), (2561, 40, 300)])
 def test_small_pool_gate(n, R, budget):
-    """Around the size up to which the gate is one launch (3072 candidates): ties, scores
-    of -inf, bad parents, NaN and chains past the depth cap."""
+    """Around the size up to which the gate is one launch (2560 candidates) and the one of
+    a front kernel without gate launches (3072): ties, scores of -inf, bad parents, NaN and
+    chains past the depth cap."""
     rng = np.random.default_rng(n + R)
     offs = np.concatenate([[0], np.sort(rng.integers(0, n + 1, R - 1)), [n]]).astype(np.int32)
     local = np.concatenate([np.arange(k) for k in np.diff(offs)]).astype(np.int64)

@@ -152,3 +152,28 @@ def test_elastic_many_or_large_requests(sizes, other, bound):
     the grants."""
     assert _ratio(f"elastic, {len(sizes)} x {sizes[0]} and {len(other)} x {other[0]}",
                   _elastic(sizes), _elastic(other)) < bound
+
+
+def _gate(R, n, levels):
+    """A call of the top-B gate over R requests of n candidates, in chains of `levels` or,
+    if 0, in trees of three children a node."""
+    import torch
+    import paper_2604_09603_amd as pkg
+    from paper_2604_09603_amd.step import _aligned_workspace
+    N = R * n
+    i = np.tile(np.arange(n), R)
+    parent = np.where(i % levels > 0, i - 1, -1) if levels else np.maximum((i - 1) // 3, -1)
+    offs, parent = _dev((np.arange(R + 1) * n).astype(np.int32)), _dev(parent.astype(np.int32))
+    logq = _dev(-np.random.default_rng(N).exponential(1.0, N).astype(np.float32))
+    score, num = torch.zeros(N, device="cuda:0"), _i32(1)
+    sel = torch.zeros(N, dtype=torch.uint8, device="cuda:0")
+    ws = _aligned_workspace(pkg.gate_workspace_size(R, N, 256), "cuda:0")
+    return lambda: pkg.echo_gate(offs, parent, logq, R, N, 256, score, sel, num, ws)
+
+
+@pytest.mark.parametrize("deep,flat,bound", [((1, 200), (4, 52), 1.65), ((4, 768), (1, 3072), 1.37)])
+def test_gate_deep_chains(deep, flat, bound):
+    """Small pools of chains of 16 levels against trees: 1.49 and 1.18; 1.81 and 1.57 with
+    two barriers per level and one launch up to 3072 candidates."""
+    assert _ratio(f"gate, {deep} in chains and {flat} in trees", _gate(*deep, 16),
+                  _gate(*flat, 0)) < bound
