@@ -421,6 +421,151 @@ def test_wide_units_infinite_value(slots, keys):
         assert np.abs(g[..., fin] - want[..., fin]).max() <= 1e-5
 
 
+def _late_key_inputs(R, slots, keys, G, early, late, seed):
+    """One KV head, `slots` slots a request (a chain), `keys` keys: every query of a
+    request is one vector, and three keys are that vector scaled: two early ones, each
+    with about a sixth of every row's weight, and a late one, one unit of log2 above them,
+    with a third; the other logits are of order 0.25.  Device tensors and host copies."""
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    normal = lambda *s, scale=1.0: (torch.empty(s, device="cuda:0").normal_(  # noqa: E731
+        generator=gen) * scale).bfloat16()
+    scale = 128 ** -0.5
+    q0 = normal(R, 128)
+    q = q0[:, None, None, :].expand(R, slots, G, 128).reshape(R * slots, G, 128).contiguous()
+    kc, vc = normal(R, keys, 1, 128, scale=0.25), normal(R, keys, 1, 128, scale=4.0)
+    unit = q0.float() / (q0.float().square().sum(1, keepdim=True) * scale)
+    for e in early:
+        kc[:, e, 0] = (unit * (math.log(keys) - math.log(2.0))).bfloat16()
+    kc[:, late, 0] = (unit * math.log(keys)).bfloat16()
+    kn, vn = normal(R * slots, 1, 128, scale=0.25), normal(R * slots, 1, 128, scale=4.0)
+    return q, kn, vn, kc.reshape(R * keys, 1, 128), vc.reshape(R * keys, 1, 128), scale
+
+
+@pytest.mark.parametrize("slots", [1, 2, 3])
+@pytest.mark.parametrize("back", [1, 2])
+def test_late_dominant_key_wide_units(slots, back):
+    """test_late_dominant_key_every_row on the shared-ring kernel: 64 and 128 rows (two
+    waves take the even and the odd tiles of the same rows) and 192 (a wave takes both),
+    one request per workgroup, so that the early keys set the reference of the late one's
+    tile, whose probability 2^(1 + e) is off by up to 2^-9 of itself in bf16.  There is an
+    early key in an even and in an odd tile, and the late one is in the last (odd) or the
+    last but one (even), so that every wave and both tiles of a step are covered.  With
+    bf16 weights alone the rows are off by more than 6e-3 (computed here: 1.1e-2); with the
+    residual product 2^-17 of these weights is left and the rounding of the others, a third
+    of the weight over 2000 keys, whose errors average out (2.8e-4 seen)."""
+    import torch
+    import paper_2604_09603_amd as pkg
+    from paper_2604_09603_amd.step import _aligned_workspace
+    R = torch.cuda.get_device_properties(0).multi_processor_count
+    G, keys = 64, 2016                     # 63 prefix tiles after one tail tile
+    late = keys - 32 * back + 9
+    q, kn, vn, kc, vc, scale = _late_key_inputs(R, slots, keys, G, (5, 40), late, 10 * slots + back)
+    bits = lambda t: t.view(torch.int16)  # noqa: E731
+    mask = torch.from_numpy(np.tile((2 << np.arange(slots)) - 1, R).astype(np.int32)).to("cuda:0")
+    kvo = torch.arange(R + 1, dtype=torch.int64, device="cuda:0") * keys
+    qo = torch.arange(R + 1, dtype=torch.int32, device="cuda:0") * slots
+    nq = R * slots
+    out, lse = torch.zeros(nq, G, 128, device="cuda:0"), torch.zeros(nq, G, device="cuda:0")
+    ws = _aligned_workspace(pkg.tree_verify_attn_workspace_size(R, nq, G, 1), "cuda:0")
+    print(f"[edges] late dominant key, wide units, {slots} slots, {back} back", flush=True)
+    pkg.echo_tree_verify_attn(bits(q), bits(kn), bits(vn), bits(kc), bits(vc), kvo, R * keys, qo,
+                              mask, 1, R, nq, G, 1, 128, scale, out, lse, ws)
+    torch.cuda.synchronize()
+    worst = plain = 0.0
+    for r in range(R):
+        # all rows of a slot are one: float64 of the first, every row against it
+        a, b = r * slots, (r + 1) * slots
+        K = torch.cat([kc[r * keys:(r + 1) * keys, 0], kn[a:b, 0]]).double()
+        V = torch.cat([vc[r * keys:(r + 1) * keys, 0], vn[a:b, 0]]).double()
+        z = (q[a:b, 0].double() @ K.T.contiguous()) * float(np.float32(scale))
+        for j in range(slots):
+            z[j, keys + j + 1:] = -math.inf
+        want = torch.softmax(z, 1) @ V
+        worst = max(worst, float((out[a:b].double() - want[:, None]).abs().max()))
+        p = torch.exp(z - z[:, 5:6]).bfloat16().double()  # the first early key's reference
+        plain = max(plain, float((p @ V / p.sum(1, keepdim=True) - want).abs().max()))
+    print(f"[edges] late dominant key, wide units: {worst:.2e} (bf16 weights alone {plain:.2e})",
+          flush=True)
+    assert plain > 6e-3
+    assert worst <= 1.5e-3, f"max abs error {worst:.3e}: the late tile's residual product did not run"
+
+
+def _ring_case(hq, hkv, slots, keys, seed, rows=None, paged=False):
+    """Requests of the given slots (chains) and keys, every row or the given slots against
+    the oracle; paged: the paged call gives the same bits."""
+    import types
+    from tests.test_gpu_serve import run_paged, to_pages
+    import torch
+    import paper_2604_09603_amd as pkg
+    from paper_2604_09603_amd.step import _aligned_workspace
+    rng = np.random.default_rng(seed)
+    R, nq, T, W = len(slots), sum(slots), sum(keys), (max(slots) + 31) // 32
+    qo = np.concatenate([[0], np.cumsum(slots)]).astype(np.int32)
+    kvo = np.concatenate([[0], np.cumsum(keys)]).astype(np.int64)
+    mask = np.zeros((nq, W), np.uint32)
+    for r, n in enumerate(slots):
+        for j in range(n):
+            for w in range(W):
+                k = min(max(j + 1 - 32 * w, 0), 32)
+                mask[qo[r] + j, w] = np.uint32((1 << k) - 1)
+    q, kn, vn = _bf16(rng, nq, hq, 128), _bf16(rng, nq, hkv, 128), _bf16(rng, nq, hkv, 128)
+    kc, vc = _bf16(rng, T, hkv, 128, scale=2.0), _bf16(rng, T, hkv, 128)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")  # noqa: E731
+    i16 = lambda a: dev(a.view(np.int16))  # noqa: E731
+    out = torch.full((nq, hq, 128), float("nan"), device="cuda:0")
+    lse = torch.full((nq, hq), float("nan"), device="cuda:0")
+    ws = _aligned_workspace(pkg.tree_verify_attn_workspace_size(R, nq, hq, hkv), "cuda:0")
+    scale = np.float32(128 ** -0.5)
+    pkg.echo_tree_verify_attn(i16(q), i16(kn), i16(vn), i16(kc), i16(vc), dev(kvo), T, dev(qo),
+                              dev(mask.view(np.int32)), W, R, nq, hq, hkv, 128, float(scale), out,
+                              lse, ws)
+    torch.cuda.synchronize()
+    out, lse = out.cpu().numpy(), lse.cpu().numpy()
+    rows = list(range(nq)) if rows is None else rows
+    ro, rl, _ = oracle.tree_verify_attn(q, kn, vn, kc, vc, kvo, qo, mask, hq, hkv, scale, rows=rows)
+    err = gc.compare_attn(out, lse, ro, rl, rows)
+    print(f"[edges] ring: max abs {err[0]:.2e}, row rel {err[1]:.2e}", flush=True)
+    if paged:
+        cfg = types.SimpleNamespace(R=R, budget=nq - R, hq=hq, hkv=hkv, mask_words=W)
+        b = dict(cfg=cfg, q=q, k_new=kn, v_new=vn, sm_scale=scale)
+        kp, vp, bt, plen = to_pages(kc, vc, kvo, 256, rng)
+        po, pl, status = run_paged(b, dict(q_offsets=qo, tree_mask=mask), kp, vp, bt, plen, 256)
+        assert status == 0
+        assert np.array_equal(po.view(np.uint32), out.view(np.uint32))
+        assert np.array_equal(pl.view(np.uint32), lse.view(np.uint32))
+
+
+def test_wide_units_ring_wraps_every_row():
+    """20 to 25 tiles per workgroup on the shared-ring kernel: the ring wraps, copies run
+    inside the tile loop, and ranges hold odd and even segments of units with up to 64, up
+    to 128 (two waves share the keys) and more rows, one of two passes, whose lengths
+    differ by single tiles and keys.  Every row."""
+    slots = [5, 2, 4, 9, 1, 8, 3, 6]
+    keys = [9000, 12001, 8191, 10016, 7999, 11040, 9967, 10001]
+    print("[edges] ring wraps, 64/2 heads", flush=True)
+    _ring_case(64, 2, slots, keys, 3, paged=True)
+
+
+def test_wide_units_one_head_every_row():
+    """Few rows over one KV head (two waves of two SIMDs share the keys): 33 tiles per
+    workgroup over units of up to 64 rows and one of 72.  Every row."""
+    import torch
+    nb = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 33 * 32 * nb // 5
+    print("[edges] one head", flush=True)
+    _ring_case(8, 1, [3, 1, 9, 4, 8], [n, n + 33, n - 31, n + 1, n + 7], 4)
+
+
+def test_wide_units_long_ranges():
+    """More than 512 tiles per workgroup, so that the table of the copies' sources is
+    refilled inside a segment and between segments: 33 passes of one head over 140,003
+    keys.  Rows of three slots; the paged call bit for bit."""
+    print("[edges] long ranges, 64/1 heads, 129 slots", flush=True)
+    _ring_case(64, 1, [129], [140003], 5, rows=[0, 77, 128], paged=True)
+
+
 def _check_mask_only(b, offset):
     """echo_build_tree_mask on the oracle's selection stored `offset` bytes past a
     16-byte boundary: every output equal to the oracle's."""

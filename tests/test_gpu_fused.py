@@ -158,11 +158,11 @@ def test_fused_step_long_requests():
     (1, 4, False), (1024, 64, False), (3071, 300, False), (3072, 300, True), (3072, 16000, False),
     (3073, 300, False), (8192, 300, True), (8193, 300, True), (30000, 12000, False)])
 def test_fused_step_front_modes(n, budget, flat):
-    """Every way in which the front kernel finds the selection, on both sides of
-    where it changes: a pool of up to 3072 candidates without gate launches, the
+    """The ways in which the front kernel finds the selection, on both sides of
+    where they change: a pool of up to 3072 candidates without gate launches, the
     lists of the select launch up to the 8192 entries that LDS takes (flat: all
-    scores equal, so that every candidate is in the threshold bin), and the flags
-    beyond that."""
+    scores equal, so that every candidate is in the threshold bin), and the
+    gate's last phase and the flags beyond that, within the lists' launch."""
     rng = np.random.default_rng(n + budget)
     R = min(n, 37)
     cuts = np.sort(rng.integers(0, n + 1, R - 1))
@@ -176,3 +176,42 @@ def test_fused_step_front_modes(n, budget, flat):
                 root_token=rng.integers(0, 5, R).astype(np.int32))
     _log(f"[fused] front modes N={n} B={budget} flat={flat}")
     _compare(make_micro_batch(pool, budget, hq=8, hkv=4, p_range=(0, 40), seed=n), repeat=2)
+
+
+@pytest.mark.parametrize("R,n,budget", [(4095, 3000, 200), (1025, 3072, 1000), (2000, 20000, 300),
+                                        (4095, 9000, 4000), (37, 30000, 16000)])
+def test_fused_step_front_modes_sizes(R, n, budget):
+    """More requests than the front kernel has threads (1024), from a small pool and from
+    lists: the planning workgroup reads back the slot offsets that it has just written.
+    And a budget whose tables leave no LDS for the lists: the launch that reads flags."""
+    rng = np.random.default_rng(n + R)
+    cuts = np.sort(rng.integers(0, n + 1, R - 1))
+    offs = np.concatenate([[0], cuts, [n]]).astype(np.int32)
+    local = np.concatenate([np.arange(k) for k in np.diff(offs)])
+    parent = np.where(rng.random(n) < 0.3, -1, (local - 1) // 2).astype(np.int32)
+    logq = rng.choice(np.array([0.0, -0.25, -0.5, -1.0, -3.0, -np.inf], np.float32), n)
+    pool = dict(cand_offsets=offs, parent=parent, token=rng.integers(0, 5, n).astype(np.int32),
+                logq=logq, root_token=rng.integers(0, 5, R).astype(np.int32))
+    _log(f"[fused] front modes R={R} N={n} B={budget}")
+    _compare(make_micro_batch(pool, budget, hq=8, hkv=4, p_range=(0, 40), seed=n), repeat=2)
+
+
+@pytest.mark.parametrize("n", [900, 5000])
+@pytest.mark.parametrize("fault", ["start", "order"])
+def test_fused_step_malformed_csr(n, fault):
+    """A candidate CSR that does not start at 0 or decreases, for a small pool and for
+    lists: nothing is selected and every request keeps its root."""
+    rng = np.random.default_rng(n)
+    offs = np.linspace(0, n, 8).astype(np.int32)
+    if fault == "start":
+        offs[0] = 1
+    else:
+        offs[3], offs[4] = offs[4], offs[3]
+    parent = np.full(n, -1, np.int32)
+    pool = dict(cand_offsets=offs, parent=parent, token=rng.integers(0, 5, n).astype(np.int32),
+                logq=rng.uniform(-3, 0, n).astype(np.float32),
+                root_token=rng.integers(0, 5, 7).astype(np.int32))
+    _log(f"[fused] malformed CSR N={n} {fault}")
+    res = _compare(make_micro_batch(pool, 50, hq=8, hkv=4, p_range=(0, 40), seed=n))
+    assert res["status"] & oracle.status.BAD_OFFSETS
+    assert res["num_selected"] == 0 and res["num_slots"] == 7
