@@ -13,8 +13,8 @@
 // keys within a product of P V is the one in which S^T leaves them in the lanes (V
 // is read in the same order).
 //
-// What bounds it (16 requests of 16384-32768 keys, 64 / 4 heads, 208 rows per head;
-// builds that skip work): copies alone 144-155 us (805 MB), arithmetic alone 191-210,
+// What bounds it (16 requests of 16384-32768 keys, 64 / 4 heads, 208 rows per head; from
+// builds that skip work and from short probes, neither of them kept): copies alone 144-155 us (805 MB), arithmetic alone 191-210,
 // both 230-275 (the ordinary kernel: 289-326; the first figure of each pair is the
 // best launch, the second the median of launches back to back, at a lower clock).
 // With one KV head (128 requests of 1024-8192 keys, 48 rows): 50-52, 45-49 and 62-66
@@ -197,7 +197,8 @@ template <int NT>
 __device__ __forceinline__ void wide_scores(uint32_t stg, uint32_t ka, const bf16x8 (&qf)[8],
                                             floatx16 (&s)[NT]) {
   // (opaque: the fragments' addresses are formed per step, not kept in registers;
-  // stages are 16 KB aligned, so the swizzle's exclusive-or may follow the sum)
+  // the ring starts at a multiple of 1 KB, so the swizzle's exclusive-or, of bits below
+  // 256, may follow the sum)
   ka += stg;
   asm volatile("" : "+v"(ka));
   bf16x8 kf[NT][8];
@@ -397,7 +398,9 @@ __device__ __forceinline__ void wide_merge(char* xchg, int rblock, int nrb, int 
 // All but the copies of the `later` youngest positions of this wave have landed.
 // (Stores in flight can only make the wait longer: loads return in order.)
 __device__ __forceinline__ void wide_wait(int later) {  // uniform
-  if (later >= 6) wait_vm<6 * kWideCopies>();  // the steady state
+  if (later >= 6) wait_vm<6 * kWideCopies>();  // a range's first step: all eight were sent
+  // the steady state: this step's two are sent after the wait, so that four stages of the
+  // eight are in flight at it and six after it
   else if (later >= 4) wait_vm<4 * kWideCopies>();
   else if (later >= 2) wait_vm<2 * kWideCopies>();
   else wait_vm<0>();

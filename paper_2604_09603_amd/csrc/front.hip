@@ -206,7 +206,8 @@ size_t mode_lds(int mode, int32_t N, int32_t R, int32_t budget) {
 
 template <bool kAligned, bool kWide>
 void (*front_of(int mode))(FrontArgs) {
-  if (mode == kModeSmall) return front_kernel<kAligned, kWide, kModeSmall>;
+  // (a small pool's flags are only written, byte by byte, aligned or not)
+  if (mode == kModeSmall) return front_kernel<true, kWide, kModeSmall>;
   if (mode == kModeLists) return front_kernel<kAligned, kWide, kModeLists>;
   return front_kernel<kAligned, kWide, kModeFlags>;
 }

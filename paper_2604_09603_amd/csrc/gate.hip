@@ -1,7 +1,7 @@
 // Gate: path scores (eq. 5) and the global top-B selection under the batch
-// verification cap (eq. 4).  One launch for a small pool (gate_small), else three,
-// none of which contends on a
-// global atomic (on a multi-XCD part those serialise far from the CUs):
+// verification cap (eq. 4).  One launch for a small pool (gate_small), else three, none
+// of which contends on a global atomic (on a multi-XCD part those serialise far from the
+// CUs):
 //
 //   gate_score   one thread per candidate: root->leaf binary32 fold of the path
 //                score, 32-bit orderable key, and each block's 2048-bin histogram
@@ -15,9 +15,8 @@
 //                block's own candidate slice.
 //   gate_finish  one block: gathers the candidates into LDS, finds the
 //                threshold (key descending, index ascending) among them by radix
-//                selection, selects the head and checks the ancestor closure of
-//                the selection.  If b* holds more keys than LDS takes, the same
-//                selection runs over all keys in place.
+//                selection and selects the head.  If b* holds more keys than LDS
+//                takes, the same selection runs over all keys in place.
 //
 // Sparse checkpoint gating (eq. 6, eq. 7; Alg. 1 phase 1) adds two launches in
 // front of gate_select: gate_lmax_clear zeroes the per-(request, depth) maximum

@@ -319,10 +319,10 @@ __device__ __forceinline__ int compact_entries(int n, Sel sel, Value value, int3
 
 // The last phase of the top-B selection, one workgroup of kGateThreads: gathers
 // the candidates of the threshold bin, finds the threshold (key descending,
-// index ascending) by radix selection, writes their selection flags and checks
-// the ancestor closure of the selection.  If the bin holds more keys than LDS
-// takes, the same selection runs over all keys in place.
-__device__ void gate_finish_body(int N, int nblocks, const GateWs& ws,
+// index ascending) by radix selection and writes their selection flags.  If the
+// bin holds more keys than LDS takes, the same selection runs over all keys in
+// place.
+[[maybe_unused]] __device__ void gate_finish_body(int N, int nblocks, const GateWs& ws,
                                  uint8_t* __restrict__ selected, int32_t* status,
                                  const FinishLds& lds) {
   uint32_t* s_k = lds.s_k;
