@@ -132,8 +132,8 @@ def pmc_summary(args):
 
     Normalisation: GRBM_GUI_ACTIVE is summed over the 8 XCDs (cycles of one XCD =
     GRBM_GUI_ACTIVE / 8); SQ_VALU_MFMA_BUSY_CYCLES sums the busy cycles of the matrix
-    units of all 1024 SIMDs (16 per v_mfma_f32_16x16x32_bf16), so the MFMA busy
-    fraction is SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE / 8 * 1024); SQ_BUSY_CYCLES
+    units of all 1024 SIMDs (16 per v_mfma_f32_16x16x32_bf16, 32 per
+    v_mfma_f32_32x32x16_bf16), so the MFMA busy fraction is SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE / 8 * 1024); SQ_BUSY_CYCLES
     sums the 32 shader engines; SQ_WAVE_CYCLES and the SQ_WAIT_* counters count in the
     same (quad-cycle) unit per wave, so their ratio is the fraction of a wave's life
     spent waiting; instruction counts are per dispatch and divided by SQ_WAVES;
@@ -141,10 +141,10 @@ def pmc_summary(args):
     are scaled by what they read for a plain device copy of known size."""
     counters, samples = {}, {}
     for d in args.pmc_summary:
-        m, n = _pmc_medians(d)
+        m, n = _pmc_medians(d, kernel=args.pmc_kernel)
         counters.update(m)
         samples.update(n)
-    out = {"kernel": "attn_main_kernel",
+    out = {"kernel": args.pmc_kernel,
            "workload_key": {"config": args.config, "seed": args.seed, "gate_policy": args.gate_policy,
                             "page_size": args.page_size, "serve": bool(args.serve)},
            "attn_src_sha256": attn_source_hash(), "counters_median_per_dispatch": counters,
@@ -189,7 +189,7 @@ def pmc_summary(args):
     with open(args.pmc_out + ".json", "w") as f:
         json.dump(out, f, indent=1)
     from synth.configs import DESCRIPTION
-    lines = [f"# rocprofv3 counters of attn_main_kernel, {DESCRIPTION.get(args.config, args.config)}, "
+    lines = [f"# rocprofv3 counters of {args.pmc_kernel}, {DESCRIPTION.get(args.config, args.config)}, "
              f"seed {args.seed}", "", "Passes (each its own run, from the repository root as $REPO):",
              "", "```"] + list(args.pmc_commands) + ["```", "",
              "| counter | median per dispatch |", "|---|---|"]
@@ -386,6 +386,9 @@ def main():
                     help="only summarise rocprofv3 --pmc output directories of the attention "
                          "kernel (the counter passes of --config/--seed, then the FETCH_SIZE and "
                          "WRITE_SIZE passes of --copy-calibration) into --pmc-out .json/.md")
+    ap.add_argument("--pmc-kernel", default="attn_main_kernel",
+                    help="with --pmc-summary: the kernel (attn_wide_kernel where the workload's "
+                         "rows or heads select it)")
     ap.add_argument("--pmc-copy", nargs=2, metavar=("FETCH_DIR", "WRITE_DIR"),
                     help="with --pmc-summary: the copy-calibration passes")
     ap.add_argument("--pmc-copy-bytes", type=int, default=1 << 30)
@@ -671,7 +674,8 @@ def main():
             **timing_extra,
         },
         "roofline": {
-            "kernel": "attn_main_kernel",
+            "kernel": "the attention's main kernel (attn_main_kernel, or attn_wide_kernel where "
+                      "the workload's rows or heads select it)",
             "bound": "hbm",
             "achieved": achieved_gbs,
             "peak": PEAK_HBM_GBS,
